@@ -98,11 +98,11 @@ extern "C" int rm_autotune_score(const rm_index* idx, int32_t n_groups,
   rm_tuning best_c{0, 0};
   int status = RM_OK;
   for (const rm_tuning& c : cands) {
-    size_t need = rm_score_groups_workspace_bytes(idx, n_groups, n_reads, k_fetch, &c);
-    if (need == 0 || need > ws_bytes) continue;
+    if (rm_score_groups_workspace_bytes(idx, n_groups, n_reads, k_fetch, &c) == 0) continue;
     // warm-up run, then one timed run
     int st = rm_score_topk_groups(idx, n_groups, d_read_emb, d_read_scale, n_reads, k_fetch,
                                   d_cand_idx, d_cand_score, d_ws, ws_bytes, &c, stream);
+    if (st == RM_ESIZE) continue;  // no plan of this shape fits the workspace
     if (st != RM_OK) {
       status = st;
       break;

@@ -264,6 +264,9 @@ struct ScoreGroup {
   int32_t item_begin;        // first work item of this group
   int32_t thin;              // 1: read tiles of half the block's reads (a group whose
                              // reads would leave most of a full tile empty)
+  int32_t seed_begin;        // first block of the group's seed launch
+  int32_t seed_segs;         // its blocks per 128 reads (0: not seeded)
+  int32_t seed_tiles;        // 32-window tiles per block
   uint64_t* lists;           // [R][P][kp] keys
   uint32_t* gthr;            // [R] shared k-th-best per read
   uint64_t* gslot;           // [R][kScoreSlots] keys of finished chunks (slot = id mod kScoreSlots)

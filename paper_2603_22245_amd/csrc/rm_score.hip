@@ -4,6 +4,8 @@
 // rm_score_f16.hip.
 #include "rm_score_kernel.h"
 
+#include <algorithm>
+
 namespace rm {
 
 namespace {
@@ -22,27 +24,28 @@ __global__ void clear_state(ScoreLaunch L) {
     }
 }
 
+// Keys per read that merge_kernel takes, and that merge_block_kernel takes.
+constexpr int kMergeKeys = 1024, kMergeKeysWide = 16384;
+// One block per CU of the chip; the items of a launch with few read tiles;
+// the reads of a single group up to which read tiles hold 128.
+constexpr int64_t kChipBlocks = 256, kMaxItems = 8 * kChipBlocks;
+constexpr int32_t kFewReads = 1024;
+
 // Merge the P per-chunk lists of each read into its k_fetch best (keys are
 // unique per read).  One wavefront per read (all its lanes active): each lane
 // sorts the EMAX keys it holds (descending), then every round takes the
 // wavefront maximum of the lanes' heads and the lane that held it drops its
 // head.  Lane `out` keeps the
 // round-`out` winner, so the k_fetch results are written with one coalesced
-// store each.
+// store each.  wave_best: that reduction of n keys.
 template <int EMAX>
-__global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__ ws, int n_per_read,
-                                                    int32_t R, int k_fetch,
-                                                    int32_t* __restrict__ cand_idx,
-                                                    float* __restrict__ cand_score) {
-  const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= R) return;
-  const uint64_t* src = ws + r * n_per_read;
+__device__ __forceinline__ uint64_t wave_best(const uint64_t* __restrict__ src, int n, int k,
+                                              int lane) {
   uint64_t mine[EMAX];
 #pragma unroll
   for (int e = 0; e < EMAX; ++e) {
     int i = e * 64 + lane;
-    mine[e] = i < n_per_read ? src[i] : 0;
+    mine[e] = i < n ? src[i] : 0;
   }
   // odd-even transposition sort, descending (EMAX rounds make it complete)
 #pragma unroll
@@ -54,7 +57,7 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__
       mine[e + 1] = x > y ? y : x;
     }
   uint64_t res = 0;
-  for (int out = 0; out < k_fetch; ++out) {
+  for (int out = 0; out < k; ++out) {
     const uint64_t gbest = wave_max_u64(mine[0]);
     if (gbest != 0 && mine[0] == gbest) {
 #pragma unroll
@@ -63,9 +66,129 @@ __global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__
     }
     if (lane == out) res = gbest;
   }
+  return res;
+}
+
+template <int EMAX>
+__global__ __launch_bounds__(256) void merge_kernel(const uint64_t* __restrict__ ws, int n_per_read,
+                                                    int32_t R, int k_fetch,
+                                                    int32_t* __restrict__ cand_idx,
+                                                    float* __restrict__ cand_score) {
+  const int lane = threadIdx.x & 63;
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= R) return;
+  const uint64_t res = wave_best<EMAX>(ws + r * n_per_read, n_per_read, k_fetch, lane);
   if (lane < k_fetch) {
     write_list_entry(res, &cand_idx[r * k_fetch + lane], &cand_score[r * k_fetch + lane]);
   }
+}
+
+// The same merge for few reads with many chunks (n_per_read up to
+// kMergeKeysWide, 16 keys per lane of the block): 16 wavefronts per read, each
+// reducing a sixteenth of the keys to its k_fetch best, then the first
+// wavefront those.  Latency bound; one wavefront per read would hold 256 keys
+// per lane.
+constexpr int kMergeWaves = 16;
+template <int EMAX>
+__global__ __launch_bounds__(64 * kMergeWaves) void merge_block_kernel(
+    const uint64_t* __restrict__ ws, int n_per_read, int k_fetch, int32_t* __restrict__ cand_idx,
+    float* __restrict__ cand_score) {
+  __shared__ uint64_t best[kMergeWaves * RM_MAX_KFETCH];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t r = blockIdx.x;
+  const int per = (n_per_read + kMergeWaves - 1) / kMergeWaves, from = wave * per;
+  const uint64_t key = wave_best<EMAX>(ws + r * n_per_read + from, min(per, n_per_read - from),
+                                       k_fetch, lane);
+  if (lane < k_fetch) best[wave * k_fetch + lane] = key;
+  __syncthreads();
+  if (wave != 0) return;
+  const uint64_t res = wave_best<16>(best, kMergeWaves * k_fetch, k_fetch, lane);
+  if (lane < k_fetch) {
+    write_list_entry(res, &cand_idx[r * k_fetch + lane], &cand_score[r * k_fetch + lane]);
+  }
+}
+
+// Seeds the reads' slots before the scoring launch, so that no chunk starts
+// without a threshold.  A block of eight wavefronts scores 128 reads against
+// seed_tiles of the 32-window tiles sampled evenly over the index; a lane
+// keeps, per read, the largest F of its column over these tiles, with no
+// lists and no test.  Windows of different columns are different windows
+// (slot = id mod 32 = column), so the columns' maxima are exactly what the
+// slots hold, and the KP-th largest of them bounds the read's KP-th best
+// from below (slot_bounds, at the start of every scoring item).  A key's low
+// word names a window, but the bound only uses its F.
+// Without it every chunk of a small launch fills its own lists from nothing
+// (16 to 60 appends and 2 to 4 merges per read and chunk), which took most of
+// the time: 200 reads against 20,000 FP16 windows 465 -> 90 us, 1,000 reads
+// against 100,000 509 -> 230 us, 100 reads against 10^7 2.3 -> 1.1 ms.  Both
+// operands come straight from global memory (the block's wavefronts read the
+// same window rows): latency and L1 bound, about a third of the scoring
+// kernel's rate per score, over at most a few percent of its scores.
+template <int PREC, int KR>
+__global__ __launch_bounds__(512) void seed_kernel(ScoreLaunch L) {
+  using RF = RowFmt<PREC, KR>;
+  constexpr bool kFp8 = PREC == RM_FP8_E4M3;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 5, col = lane & 31;
+  int gi = 0;
+  while (gi + 1 < L.n_groups && (int)blockIdx.x >= L.g[gi + 1].seed_begin) ++gi;
+  const ScoreGroup& G = L.g[gi];
+  const int local = blockIdx.x - G.seed_begin;
+  const int seg = local % G.seed_segs;
+  const int64_t R = G.R, W = G.W;
+  const int64_t read0 = ((int64_t)(local / G.seed_segs) * 8 + wave) * 16;
+  if (read0 >= R) return;
+  uint4 a[1][RF::AU4];
+  const int64_t arow = 2 * read0 + col;
+#pragma unroll
+  for (int u = 0; u < RF::AU4; ++u)
+    a[0][u] = arow < 2 * R ? reinterpret_cast<const uint4*>(G.reads + arow * RF::RB)[RF::lane_chunk(g, u)]
+                           : make_uint4(0, 0, 0, 0);
+  float m[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) m[q] = -1.f;
+  const int64_t all = (W + kBlkW - 1) / kBlkW, n = (int64_t)G.seed_segs * G.seed_tiles;
+  for (int t = 0; t < G.seed_tiles; ++t) {
+    const int64_t j = ((int64_t)seg * G.seed_tiles + t) * all / n * kBlkW + col;
+    const int64_t row = min(j, W - 1);
+    const uint4* src = reinterpret_cast<const uint4*>(G.index + row * RF::RB);
+    uint4 b[RF::AU4];
+#pragma unroll
+    for (int u = 0; u < RF::AU4; ++u) b[u] = src[RF::lane_chunk(g, u)];
+    f32x16 acc{};
+    mfma_regs<PREC, KR>(a[0], b, acc);
+    float sj2 = 1.f;
+    if constexpr (kFp8) {
+      const float sc = G.win_scale[row];
+      sj2 = sc * sc;
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const float re = acc[2 * q], im = acc[2 * q + 1];
+      const float F = (re * re + im * im) * sj2;
+      m[q] = j < W ? fmaxf(m[q], F) : m[q];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int64_t r = read0 + 4 * (q >> 1) + 2 * g + (q & 1);
+    if (r >= R || m[q] < 0.f) continue;
+    float F = m[q];
+    if constexpr (kFp8) F *= G.read_scale[r] * G.read_scale[r];
+    const uint64_t key = make_key(F, -1);
+    unsigned long long* slot =
+        reinterpret_cast<unsigned long long*>(&G.gslot[r * kScoreSlots + col]);
+    if (key > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(slot, (unsigned long long)key);
+  }
+}
+
+template <int PREC>
+hipError_t launch_seed(bool reduced, int blocks, const ScoreLaunch& L, hipStream_t s) {
+  hipLaunchKernelGGL((reduced ? seed_kernel<PREC, kRealReduced> : seed_kernel<PREC, kReal>),
+                     dim3((unsigned)blocks), dim3(512), 0, s, L);
+  return hipGetLastError();
 }
 
 // Instantiations: (precision, reads per block, list length, row format) ->
@@ -124,12 +247,20 @@ ScorePlan plan_score(int precision, int n_groups, const int64_t* W, const int32_
   ScorePlan p{};
   p.kp = k_fetch <= 8 ? 8 : k_fetch <= 16 ? 16 : k_fetch <= 32 ? 32 : 64;
   int rt = t.read_tile;
-  if (rt == 0) rt = read_tile_ok(precision, p.kp, 256) ? 256 : 128;
+  if (rt == 0) {
+    // 128-read tiles leave room for two blocks per CU and lose less to a
+    // part-filled tile: up to 1,024 reads they are the faster ones (FP16, 200
+    // reads x 20,000 windows 101 -> 86 us, 1,000 x 100,000 238 -> 225 us, 100
+    // x 10^7 1.18 -> 1.11 ms), beyond that the wider tile's reuse of each
+    // window is (2,000 x 10^6: 1.79 against 1.84 ms)
+    const bool few = n_groups == 1 && R[0] <= kFewReads;
+    rt = !few && read_tile_ok(precision, p.kp, 256) ? 256 : 128;
+  }
   if (!read_tile_ok(precision, p.kp, rt) || n_groups < 1 || n_groups > kMaxGroups) return p;
   p.read_tile = rt;
   p.n_groups = n_groups;
-  size_t off = 0;
-  int64_t items = 0;
+  // work of a group: 64-window units x 128-read halves of its read tiles
+  int64_t work[kMaxGroups], total_work = 0;
   for (int i = 0; i < n_groups; ++i) {
     GroupPlan& gp = p.g[i];
     gp.read_tiles = (int)(((int64_t)R[i] + rt - 1) / rt);
@@ -144,29 +275,63 @@ ScorePlan plan_score(int precision, int n_groups, const int64_t* W, const int32_
         gp.read_tiles = (int)t128;
       }
     }
-    int64_t tiles = (W[i] + kPlanW - 1) / kPlanW;
-    int64_t ct = t.chunk_tiles;
+    work[i] = (W[i] + kPlanW - 1) / kPlanW * gp.read_tiles * (rt == 256 && !gp.thin ? 2 : 1);
+    total_work += work[i];
+  }
+  size_t off = 0;
+  int64_t items = 0;
+  for (int i = 0; i < n_groups; ++i) {
+    GroupPlan& gp = p.g[i];
+    const int64_t tiles = (W[i] + kPlanW - 1) / kPlanW;
+    int64_t ct = t.chunk_tiles, most = kMergeKeys / p.kp;
     if (ct <= 0) {
       // about 30 items per CU of a 256-CU chip (a short last round), at least
       // 64 tile units each, at most 1024 keys per read for the merge; fewer,
       // longer items leave an uneven last round, more items repeat each
       // read's top-k warm-up in more chunks
-      int64_t P = (256 * 30 + gp.read_tiles - 1) / gp.read_tiles;
-      if (P > (tiles + 63) / 64) P = (tiles + 63) / 64;
-      if (P < 1) P = 1;
+      int64_t P = (kChipBlocks * 30 + gp.read_tiles - 1) / gp.read_tiles;
+      P = std::min({P, (tiles + 63) / 64, most});
+      // Few read tiles: that rule gives 64 chunks of 16-key lists at most,
+      // and one per 4,096 windows (10 items for 200 FP32 reads against
+      // 20,000 windows).  Here a group gets its share of eight items per CU
+      // with chunks of 2,048 windows or more, but at least its share of one
+      // per CU, and a single group fills whole rounds of the chip.  Measured
+      // (chunks before -> now): FP32 200 x 20,000 1,330 -> 165 us (5 -> 104),
+      // FP16 8 x 10^7 2,310 -> 725 us (64 -> 512), 300 x 10^6 970 -> 440 us.
+      // Up to 32 reads the launch only streams the index, and shorter
+      // chunks cost more than they balance (8 x 10^7: 512 chunks 724 us,
+      // 1,024 775 us).
+      most = std::max<int64_t>(most, kMergeKeysWide / p.kp);
+      const int64_t share = (work[i] * kChipBlocks + total_work - 1) / total_work;
+      int64_t Q = std::min(8 * share / gp.read_tiles, (tiles + 31) / 32);
+      Q = std::max(Q, (share + gp.read_tiles - 1) / gp.read_tiles);
+      if (R[i] <= 32) Q = std::min<int64_t>(Q, 2 * kChipBlocks);
+      if (n_groups == 1) {
+        const int64_t rounds = (Q * gp.read_tiles + kChipBlocks - 1) / kChipBlocks;
+        Q = std::max(Q, rounds * kChipBlocks / gp.read_tiles);
+      }
+      P = std::max(P, std::min({Q, most, tiles}));
+      P = std::max<int64_t>(P, 1);
       ct = (tiles + P - 1) / P;
     }
     if (ct < 1) ct = 1;
     int64_t P = (tiles + ct - 1) / ct;
-    if (P > 1024 / p.kp) {  // keep the merge within 1024 keys per read
-      P = 1024 / p.kp;
+    if (P > most) {  // keep the merge within its keys per read
+      P = most;
       ct = (tiles + P - 1) / P;
       P = (tiles + ct - 1) / ct;
     }
     gp.chunk_windows = ct * kPlanW;
     gp.chunks = (int)P;
     gp.lists_offset = off;
-    off = align256(off + (size_t)R[i] * (size_t)P * (size_t)p.kp * sizeof(uint64_t));
+    int64_t keys = (int64_t)R[i] * P;
+    // A default plan's chunks times read tiles stay within kMaxItems (or the
+    // windows' own units), whatever the reads: room for that many keeps the
+    // workspace of more reads large enough for fewer.
+    if (t.chunk_tiles <= 0)
+      keys = std::max(keys, (R[i] <= kFewReads ? 128 : rt) *
+                                std::min(kMaxItems, std::max(2 * kChipBlocks, tiles)));
+    off = align256(off + (size_t)keys * (size_t)p.kp * sizeof(uint64_t));
     gp.thr_offset = off;
     off = align256(off + (size_t)R[i] * sizeof(uint32_t));
     gp.slot_offset = off;
@@ -191,6 +356,7 @@ hipError_t launch_score_topk(const rm_index* idx, const ScorePlan& plan,
   L.counter = reinterpret_cast<int*>(base + plan.counter_offset);
   int32_t item = 0;
   int32_t maxR = 0;
+  int32_t seed_blocks = 0;
   for (int i = 0; i < plan.n_groups; ++i) {
     const GroupPlan& gp = plan.g[i];
     ScoreGroup& G = L.g[i];
@@ -205,6 +371,25 @@ hipError_t launch_score_topk(const rm_index* idx, const ScorePlan& plan,
     G.P = gp.chunks;
     G.item_begin = item;
     G.thin = gp.thin;
+    G.seed_begin = seed_blocks;
+    // Seeding pays while a read's chunks run in few rounds of the chip: with
+    // more than 12 the later rounds start from the earlier ones' slots and the
+    // first round's lists cost less than the sample (20,000 reads against 10^6
+    // windows, 20 rounds: 15.1 ms without, 15.1-15.6 ms with; 5,000 reads, 5
+    // rounds: 4.60 -> 4.30 ms).  A grouped launch, whose groups share the
+    // rounds, takes a larger sample (7 groups of 5,000 reads, FP8: 10.7 ms
+    // without, 7.9 with a 64th, 7.3 with a 32nd).
+    // FP32 scores cost eight times as much against the same lists: two rounds.
+    const int64_t rounds = idx[0].p.precision == RM_FP32 ? 2 : 12;
+    if (plan.kp <= kScoreSlots && (int64_t)gp.read_tiles * gp.chunks <= rounds * kChipBlocks) {
+      const int64_t sample = std::min<int64_t>(
+          std::max<int64_t>(G.W / (plan.n_groups > 1 ? 16 : 64), 8192), 65536);
+      const int64_t n = (std::min(G.W, sample) + kBlkW - 1) / kBlkW, tiles = ((int64_t)R[i] + 127) / 128;
+      // 2 to 8 tiles per block, fewer where that fills the chip twice
+      G.seed_tiles = (int)std::min<int64_t>(std::max<int64_t>(n * tiles / (2 * kChipBlocks), 2), 8);
+      G.seed_segs = (int)((n + G.seed_tiles - 1) / G.seed_tiles);
+      seed_blocks += G.seed_segs * (int)tiles;
+    }
     G.lists = reinterpret_cast<uint64_t*>(base + gp.lists_offset);
     G.gthr = reinterpret_cast<uint32_t*>(base + gp.thr_offset);
     G.gslot = reinterpret_cast<uint64_t*>(base + gp.slot_offset);
@@ -214,17 +399,31 @@ hipError_t launch_score_topk(const rm_index* idx, const ScorePlan& plan,
   hipLaunchKernelGGL(clear_state, dim3((unsigned)(((int64_t)maxR + 255) / 256)), dim3(256), 0, s, L);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (seed_blocks > 0) {
+    const bool red = reduced_rows(idx[0].p);
+    e = idx[0].p.precision == RM_FP32   ? launch_seed<RM_FP32>(red, seed_blocks, L, s)
+        : idx[0].p.precision == RM_FP16 ? launch_seed<RM_FP16>(red, seed_blocks, L, s)
+                                        : launch_seed<RM_FP8_E4M3>(red, seed_blocks, L, s);
+    if (e != hipSuccess) return e;
+  }
   e = dispatch(idx[0].p.precision, reduced_rows(idx[0].p), plan.read_tile, plan.kp, L, s);
   if (e != hipSuccess) return e;
   for (int i = 0; i < plan.n_groups; ++i) {
     int n_per_read = plan.g[i].chunks * plan.kp;
+    const uint64_t* lists = reinterpret_cast<const uint64_t*>(base + plan.g[i].lists_offset);
+    if (n_per_read > kMergeKeys) {  // at most kMergeKeysWide (plan_score)
+      auto wide = n_per_read <= kMergeKeysWide / 4 ? merge_block_kernel<4> : merge_block_kernel<16>;
+      hipLaunchKernelGGL(wide, dim3((unsigned)R[i]), dim3(64 * kMergeWaves), 0, s, lists, n_per_read,
+                         k_fetch, cand_idx[i], cand_score[i]);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      continue;
+    }
     unsigned blocks = (unsigned)(((int64_t)R[i] + 3) / 4);
-    // n_per_read <= 1024 (plan_score keeps the merge within 1024 keys)
     auto kern = n_per_read <= 256 ? merge_kernel<4> : n_per_read <= 512 ? merge_kernel<8>
                                                                         : merge_kernel<16>;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s,
-                       reinterpret_cast<const uint64_t*>(base + plan.g[i].lists_offset), n_per_read,
-                       R[i], k_fetch, cand_idx[i], cand_score[i]);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, s, lists, n_per_read, R[i], k_fetch,
+                       cand_idx[i], cand_score[i]);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -315,6 +315,39 @@ __device__ __forceinline__ void mfma_tile(const uint4 (&a)[NF][RowFmt<PREC, KR>:
   }
 }
 
+// The same product with the window rows' chunks in registers (slot order of
+// RowFmt), one fragment by one column block: the same K order as mfma_tile.
+template <int PREC, int KR>
+__device__ __forceinline__ void mfma_regs(const uint4 (&a)[RowFmt<PREC, KR>::AU4],
+                                          const uint4 (&b)[RowFmt<PREC, KR>::AU4], f32x16& acc) {
+  constexpr int AU4 = RowFmt<PREC, KR>::AU4;
+  if constexpr (PREC == RM_FP16) {
+#pragma unroll
+    for (int s = 0; s < AU4; ++s)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a[s]),
+                                                   __builtin_bit_cast(half8, b[s]), acc, 0, 0, 0);
+  } else if constexpr (PREC == RM_FP8_E4M3) {
+    auto pack = [](const uint4& lo, const uint4& hi) {
+      return i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w,
+                   (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+    };
+#pragma unroll
+    for (int s = 0; s < AU4; s += 2)
+      acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(pack(a[s], a[s + 1]), pack(b[s], b[s + 1]),
+                                                            acc, 0, 0, 0, 127, 0, 127);
+  } else {
+#pragma unroll
+    for (int s = 0; s < AU4; ++s) {
+      const uint32_t av[4] = {a[s].x, a[s].y, a[s].z, a[s].w};
+      const uint32_t bv[4] = {b[s].x, b[s].y, b[s].z, b[s].w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(av[q]), __uint_as_float(bv[q]),
+                                                   acc, 0, 0, 0);
+    }
+  }
+}
+
 template <int PREC, int NF, int WAVES, int KP, int ENT, int STAGES, int NB, int KR>
 struct ScoreKernel {
   using RF = RowFmt<PREC, KR>;

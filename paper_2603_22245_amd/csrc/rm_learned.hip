@@ -11,9 +11,29 @@
 // and a pairwise logistic ranking loss on Levenshtein labels.
 //
 // Parameters: W1 [64][32], b1 [64], W2 [128][64], b2 [128], row-major, FP32.
-// One wavefront per string; lanes play two roles per token: lane j = hidden
-// unit j for the first layer, lane l = (factor l/2, letters 2(l&1), 2(l&1)+1)
-// for the offsets and the encoding, as in the encoders.
+//
+// A block of eight wavefronts takes up to eight strings.  Their tokens are
+// sorted by middle letter, two wavefronts per letter, so that the second layer
+// of a wavefront's tokens is one product with the letter's 32 rows of W2, and
+// go through the matrix cores 16 at a time:
+//   layer 1: P^T [64 x 16 tokens] = W1 [64 x 32] X^T [32 x 16].  X is one-hot,
+//     exact in bfloat16, and W1 is the exact sum of three bfloat16 parts, so
+//     three bf16 MFMAs per product are FP32 sums up to the order of additions;
+//   layer 2: O^T [32 x 16] = W2_L [32 x 64] H^T [64 x 16], both split: of the
+//     nine products of parts all but low x low (2^-32 of the product) are
+//     added.  Lane l of an accumulator holds rows 16 rb + 4 (l / 16) + v of
+//     column l % 16; eight such rows of a lane are the K entries of the next
+//     product's B operand (its A operand lists them in the same order), so no
+//     data moves;
+//   a lane then owns 8 factors of its token: phase, sine and cosine.
+// FP32 MFMAs would need no splits, but run at a sixteenth of the bf16 rate:
+// for layer 2 they cost 6 % of a step more at the same error (0.97e-7 against
+// 0.96e-7 of the gradient's 2-norm, 1.1e-7 with VALU sums).  In the backward
+// products the split doubled the error (2e-7) and is not used.
+// A step of 1,024 pairs of 150 letters takes 113 us (encoder 32, ranking 6,
+// backward 70, reduction and Adam 5); 706 us with one token at a time on the
+// VALU (189, 84, 416, 13).
+#include "rm_bf16.h"
 #include "rm_internal.h"
 
 namespace rm {
@@ -23,78 +43,214 @@ namespace {
 constexpr int kIn = 32, kHid = 64, kOut = 128;
 constexpr int kW1 = 0, kB1 = kHid * kIn, kW2 = kB1 + kHid, kB2 = kW2 + kOut * kHid;
 constexpr int kParams = kB2 + kOut;  // 10,432
-constexpr int kW2Stride = kHid + 4;  // padded LDS row of W2: conflict-free float4 reads
 constexpr int kMaxLen = 256;         // letters of a string kept in LDS
-constexpr int kWaves = 4;
-constexpr float kTau = 0.05f;
+constexpr int kMaxTok = kMaxLen - 8;
+constexpr int kStrings = 8;          // strings of a block, at most
+constexpr int kWaves = 8;
+constexpr float kInvTau = 20.f;  // of the ranking loss, 1 / 0.05
 
 static_assert(kParams == RM_LEARNED_PARAMS, "parameter count");
 
-struct Weights {  // LDS copy of the network
-  float w1t[kIn * kHid];         // W1 transposed: [input][hidden]
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// What every wavefront of a block reads of the network: W1's three bfloat16
+// parts as A fragments (rows 16 rb + lane % 16, inputs 8 (lane / 16) + 0..7),
+// and the biases.
+struct Net {
+  u32x4 w1[3][4][64];
   float b1[kHid];
-  float w2[kOut * kW2Stride];    // W2 rows padded
   float b2[kOut];
 };
 
-__device__ void load_weights(Weights& w, const float* __restrict__ p) {
-  for (int i = threadIdx.x; i < kHid * kIn; i += blockDim.x) {
-    int j = i / kIn, c = i % kIn;
-    w.w1t[c * kHid + j] = p[kW1 + i];
+__device__ __forceinline__ void load_net(Net& net, const float* __restrict__ p) {
+  const int t = threadIdx.x;
+  if (t < 256) {
+    const int rb = t >> 6, lane = t & 63;
+    const float* src = p + kW1 + (16 * rb + (lane & 15)) * kIn + 8 * (lane >> 4);
+    uint32_t part[3][8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) split_bf16x3(src[j], part[0][j], part[1][j], part[2][j]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      net.w1[q][rb][lane] =
+          u32x4{part[q][0] | part[q][1] << 16, part[q][2] | part[q][3] << 16,
+                part[q][4] | part[q][5] << 16, part[q][6] | part[q][7] << 16};
+  } else if (t < 256 + kHid) {
+    net.b1[t - 256] = p[kB1 + t - 256];
+  } else if (t < 256 + kHid + kOut) {
+    net.b2[t - 256 - kHid] = p[kB2 + t - 256 - kHid];
   }
-  for (int i = threadIdx.x; i < kHid; i += blockDim.x) w.b1[i] = p[kB1 + i];
-  for (int i = threadIdx.x; i < kOut * kHid; i += blockDim.x) {
-    int r = i / kHid, j = i % kHid;
-    w.w2[r * kW2Stride + j] = p[kW2 + i];
-  }
-  for (int i = threadIdx.x; i < kOut; i += blockDim.x) w.b2[i] = p[kB2 + i];
 }
 
-// Per-token forward pieces for the current wavefront.
-struct Token {
-  int mid;      // middle letter (>= 4: no token)
-  float pre;    // lane j: first-layer pre-activation of unit j
-  float delta;  // lane (k, hh): offset for factor k of the middle letter
-  float s, c;   // lane (k, hh): sin and cos of the phase
-};
+// max(x, 0) as one integer maximum (a positive NaN stays; fmaxf would take two
+// instructions to quiet it).
+__device__ __forceinline__ float relu(float x) {
+  return __uint_as_float((uint32_t)max(__float_as_int(x), 0));
+}
 
-// Forward of token p of the string held in `let` (LDS letters).  hbuf: this
-// wavefront's 64-float LDS scratch.
-__device__ __forceinline__ Token token_forward(const Weights& w, const uint8_t* let, int p, int N,
-                                               float* hbuf, int lane) {
-  Token t;
-  t.mid = let[p + 4];
-  // first layer: lane j sums the W1 columns selected by the 8 flanking letters
-  float pre = w.b1[lane];
+// Sine and cosine of z quarter turns: z = q + f with q the nearest integer (f
+// is exact), then the Taylor series in f on |f| <= 1/2, whose first left-out
+// terms are below 2e-9 (sine) and 2e-10 (cosine).
+__device__ __forceinline__ void sine_cosine(float z, float* sn, float* cs) {
+  const float q = rintf(z), f = z - q;
+  const float f2 = f * f;
+  float s = __builtin_fmaf(f2, 1.6044118e-4f, -4.6817541e-3f);
+  s = __builtin_fmaf(f2, s, 7.9692626e-2f);
+  s = __builtin_fmaf(f2, s, -6.4596410e-1f);
+  s = __builtin_fmaf(f2, s, 1.5707964f);
+  s *= f;
+  float c = __builtin_fmaf(f2, -2.5202042e-5f, 9.1926027e-4f);
+  c = __builtin_fmaf(f2, c, -2.0863481e-2f);
+  c = __builtin_fmaf(f2, c, 2.5366951e-1f);
+  c = __builtin_fmaf(f2, c, -1.2337006f);
+  c = __builtin_fmaf(f2, c, 1.f);
+  const int n = (int)q;
+  const float a = (n & 1) ? c : s, b = (n & 1) ? s : c;
+  *sn = __uint_as_float(__float_as_uint(a) ^ ((uint32_t)(n & 2) << 30));
+  *cs = __uint_as_float(__float_as_uint(b) ^ ((uint32_t)((n + 1) & 2) << 30));
+}
+
+// The three bfloat16 parts of eight values, packed in order.
+__device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&part)[3]) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    int f = let[p + (i < 4 ? i : i + 1)];
-    if (f < 4) pre += w.w1t[(4 * i + f) * kHid + lane];
+  for (int i = 0; i < 4; ++i) {
+    uint32_t lo[3], hi[3];
+    split_bf16x3(x[2 * i], lo[0], lo[1], lo[2]);
+    split_bf16x3(x[2 * i + 1], hi[0], hi[1], hi[2]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) part[q][i] = lo[q] | hi[q] << 16;
   }
-  t.pre = pre;
-  hbuf[lane] = fmaxf(pre, 0.f);
-  __builtin_amdgcn_wave_barrier();
-  const int k = lane >> 1, hh = lane & 1;
-  float d = 0.f;
-  if (t.mid < 4) {
-    const float* wrow = &w.w2[(t.mid * 32 + k) * kW2Stride + 32 * hh];
-    const float* hv = &hbuf[32 * hh];
+}
+__device__ __forceinline__ void split4(const f32x4& x, s16x4 (&part)[3]) {
+  uint32_t p[3][4];
 #pragma unroll
-    for (int i = 0; i < 32; i += 4) {
-      float4 a = *reinterpret_cast<const float4*>(wrow + i);
-      float4 b = *reinterpret_cast<const float4*>(hv + i);
-      d += a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w;
+  for (int i = 0; i < 4; ++i) split_bf16x3(x[i], p[0][i], p[1][i], p[2][i]);
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+    part[q] = __builtin_bit_cast(s16x4, make_uint2(p[q][0] | p[q][1] << 16, p[q][2] | p[q][3] << 16));
+}
+
+__device__ __forceinline__ f32x4 mfma32(const u32x4& a, const u32x4& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Parts (a, b) of the eight products of two split operands, smallest first.
+constexpr int kTerms = 8;
+constexpr int kTermA[kTerms] = {1, 2, 0, 2, 1, 0, 1, 0};
+constexpr int kTermB[kTerms] = {2, 1, 2, 0, 1, 1, 0, 0};
+
+// Flanks 2g and 2g + 1 of the 9-mer at `let` as a one-hot B fragment of layer 1
+// (inputs 4 i + letter of flank i; a code above 3 selects none).
+__device__ __forceinline__ u32x4 flank_fragment(const uint8_t* let, int g) {
+  const int i = 2 * g + (g > 1);  // letter 4 is the middle one
+  const uint32_t f0 = let[i], f1 = let[i + 1];
+  const uint64_t h0 = f0 < 4 ? 0x3F80ull << (16 * f0) : 0ull;
+  const uint64_t h1 = f1 < 4 ? 0x3F80ull << (16 * f1) : 0ull;
+  return u32x4{(uint32_t)h0, (uint32_t)(h0 >> 32), (uint32_t)h1, (uint32_t)(h1 >> 32)};
+}
+
+// A pre-activation this close to zero (a few dozen ulps of the summands) is
+// summed again in FP32 in the order of the flanks, so that its sign -- whether
+// the unit is on and passes gradients -- does not depend on how the matrix
+// cores add.  About one tile in 400 has one.
+constexpr float kNearZero = 1.0f / 1048576.0f;
+
+// Settles a lane's 16 pre-activations h[i / 4][i % 4]: unit(i) is the hidden unit
+// and letters(i) the 9-mer of entry i.  One at a time, so that the rare path
+// needs few registers.
+template <typename Unit, typename Letters>
+__device__ __forceinline__ void settle(const float* __restrict__ p, f32x4 (&h)[4], Unit unit,
+                                       Letters letters) {
+  float least = 1.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) least = fminf(least, fabsf(h[i >> 2][i & 3]));
+  if (!__ballot(least < kNearZero)) return;
+  uint32_t todo = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) todo |= (uint32_t)(fabsf(h[i >> 2][i & 3]) < kNearZero) << i;
+#pragma unroll 1
+  while (todo) {
+    const int at = __builtin_ctz(todo);
+    todo &= todo - 1;
+    const int u = unit(at);
+    const uint8_t* let = letters(at);
+    float pre = p[kB1 + u];
+#pragma unroll 1
+    for (int i = 0; i < 8; ++i) {
+      const int f = let[i + (i > 3)];
+      if (f < 4) pre += p[kW1 + u * kIn + 4 * i + f];
     }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) h[i >> 2][i & 3] = at == i ? pre : h[i >> 2][i & 3];
   }
-  d += __shfl_xor(d, 1, 64);
-  if (t.mid < 4) d += w.b2[t.mid * 32 + k];
-  t.delta = d;
-  // phase theta_k p + delta with the integer part reduced exactly mod N
-  int r = (int)(((int64_t)(k + 1) * p) % N);
-  float ang = 6.283185307179586f * (float)r / (float)N + d;
-  sincosf(ang, &t.s, &t.c);
-  __builtin_amdgcn_wave_barrier();  // hbuf is reused by the next token
-  return t;
+}
+
+// The letter's rows of W2 as A fragments of layer 2: rows 16 ob + lane % 16,
+// K entry j of step st = hidden unit 16 (2 st + j / 4) + 4 (lane / 16) + j % 4.
+__device__ __forceinline__ void load_w2(const float* __restrict__ p, int L, int lane,
+                                        u32x4 (&w2)[2][2][3]) {
+#pragma unroll
+  for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      const float* src = p + kW2 + (L * 32 + 16 * ob + (lane & 15)) * kHid + 32 * st + 4 * (lane >> 4);
+      float x[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[j] = src[16 * (j >> 2) + (j & 3)];
+      split8(x, w2[ob][st]);
+    }
+}
+
+// Phases of the lane's token (9-mer at `let`, its one-hot flanks x, location p): sine and cosine of
+// theta_k p + delta_k for its factors k - 1 = 16 ob + 4 g + v, index 4 ob + v.
+// k p is reduced mod N exactly: k p - q N is exact in FP32 (k p < 2^13; for an
+// N that FP32 does not hold, q = 0).
+__device__ __forceinline__ void token_phases(const float* __restrict__ params, const Net& net,
+                                             const u32x4 (&w2)[2][2][3], int L, const uint8_t* let,
+                                             const u32x4& x, int p, float Nf, float inv_n,
+                                             float turn, int lane, float (&sn)[8], float (&cs)[8]) {
+  const int g = lane >> 4;
+  f32x4 h[4];
+#pragma unroll
+  for (int rb = 0; rb < 4; ++rb) {
+    h[rb] = *reinterpret_cast<const f32x4*>(&net.b1[16 * rb + 4 * g]);
+#pragma unroll
+    for (int q = 2; q >= 0; --q) h[rb] = mfma32(net.w1[q][rb][lane], x, h[rb]);  // small parts first
+  }
+  settle(params, h, [&](int i) { return 16 * (i >> 2) + 4 * g + (i & 3); },
+         [&](int) { return let; });
+  u32x4 hp[2][3];
+#pragma unroll
+  for (int st = 0; st < 2; ++st) {
+    float hv[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) hv[j] = relu(h[2 * st + (j >> 2)][j & 3]);
+    split8(hv, hp[st]);
+  }
+  // smallest terms first over both K steps, the bias last: an accumulator
+  // that is already large loses more in each further addition
+  f32x4 o[2] = {f32x4{}, f32x4{}};
+#pragma unroll
+  for (int q = 0; q < kTerms; ++q)
+#pragma unroll
+    for (int st = 0; st < 2; ++st)
+#pragma unroll
+      for (int ob = 0; ob < 2; ++ob)
+        o[ob] = mfma32(w2[ob][st][kTermA[q]], hp[st][kTermB[q]], o[ob]);
+#pragma unroll
+  for (int ob = 0; ob < 2; ++ob)
+    o[ob] += *reinterpret_cast<const f32x4*>(&net.b2[L * 32 + 16 * ob + 4 * g]);
+  const float pf = (float)p;
+#pragma unroll
+  for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float kp = (float)(16 * ob + 4 * g + v + 1) * pf;
+      const float r = __builtin_fmaf(-rintf(kp * inv_n), Nf, kp);
+      sine_cosine(__builtin_fmaf(r, turn, o[ob][v] * 0.63661977f), &sn[4 * ob + v], &cs[4 * ob + v]);
+    }
 }
 
 // Strings come from one set (string s = seq[off[s] .. off[s+1])) or, for
@@ -106,6 +262,7 @@ struct Strings {
   const int64_t* boff;
 };
 
+// Letters of string sidx (at most kMaxLen) into LDS; returns its tokens.
 __device__ __forceinline__ int load_string(uint8_t* let, const Strings& st, int64_t sidx,
                                            int lane) {
   const uint8_t* seq = st.a;
@@ -118,33 +275,112 @@ __device__ __forceinline__ int load_string(uint8_t* let, const Strings& st, int6
     sidx >>= 1;
   }
   const int64_t a = off[sidx];
-  int n = (int)min<int64_t>(off[sidx + 1] - a, kMaxLen);
+  const int n = (int)min<int64_t>(off[sidx + 1] - a, kMaxLen);
   for (int i = lane; i < n; i += 64) let[i] = seq[a + i];
   __builtin_amdgcn_wave_barrier();
-  return n;
+  return max(n - 8, 0);
 }
 
-// Learned encodings c of n_strings strings: out[s][256] (k*4+letter, re/im).
-__global__ __launch_bounds__(64 * kWaves) void learned_encode_kernel(
-    const float* __restrict__ params, Strings st, int32_t n_strings, int N,
-    float* __restrict__ out) {
-  __shared__ Weights w;
-  __shared__ uint8_t letters[kWaves][kMaxLen];
-  __shared__ float hbuf[kWaves][kHid];
-  load_weights(w, params);
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t s = (int64_t)blockIdx.x * kWaves + wave;
-  if (s >= n_strings) return;
-  const int n = load_string(letters[wave], st, s, lane);
-  const int hh = lane & 1;
-  float2 c0 = make_float2(0.f, 0.f), c1 = make_float2(0.f, 0.f);
-  for (int p = 0; p + 9 <= n; ++p) {
-    Token t = token_forward(w, letters[wave], p, N, hbuf[wave], lane);
-    if (t.mid == 2 * hh) { c0.x += t.c; c0.y += t.s; }
-    if (t.mid == 2 * hh + 1) { c1.x += t.c; c1.y += t.s; }
+// Sum over the 16 lanes of a lane group (a DPP row), in every lane of it.
+__device__ __forceinline__ float row_sum(float v) {
+  v += dpp<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp<0x141>(v);  // row_half_mirror
+  v += dpp<0x140>(v);  // row_mirror
+  return v;
+}
+
+// F of a pair of encodings, a lane's four reals of each.
+__device__ __forceinline__ float fidelity(float4 a, float4 b) {
+  // z = sum conj(a) b
+  const float zr = wave_sum(a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w);
+  const float zi = wave_sum(a.x * b.y - a.y * b.x + a.z * b.w - a.w * b.z);
+  const float A = wave_sum(a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w);
+  const float B = wave_sum(b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w);
+  return (A > 0.f && B > 0.f) ? (zr * zr + zi * zi) / (A * B) : 0.f;
+}
+
+// Learned encodings c of n_strings strings: out[s][256] (k*4+letter, re/im);
+// for pairs (F not null) also F of strings 2i and 2i + 1.  `per` strings per block.  A string's tokens of
+// one letter fill their own 16-token tiles, so a lane sums its factors over
+// the tiles in registers and the 16 lanes are added once per string and
+// letter.
+//
+// Bound by VALU issue (the phases and the splits).
+__global__ __launch_bounds__(64 * kWaves, 2) void learned_encode_kernel(
+    const float* __restrict__ params, Strings st, int32_t n_strings, int per, float Nf,
+    float inv_n, float turn, float* __restrict__ out, float* __restrict__ F) {
+  __shared__ Net net;
+  __shared__ uint8_t letters[kStrings][kMaxLen + 8];
+  __shared__ uint8_t place[4][kStrings][kMaxLen];  // locations of a letter's tokens
+  __shared__ int tokens[4][kStrings];
+  __shared__ __align__(16) float c[kStrings][256];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t first = (int64_t)blockIdx.x * per;
+  const int n_own = (int)min<int64_t>(per, n_strings - first);
+  load_net(net, params);
+  if (wave < n_own) {
+    const int n = load_string(letters[wave], st, first + wave, lane);
+    int have[4] = {0, 0, 0, 0};
+    for (int p0 = 0; p0 < n; p0 += 64) {
+      const int mid = p0 + lane < n ? (int)letters[wave][p0 + lane + 4] : 4;
+#pragma unroll
+      for (int L = 0; L < 4; ++L) {
+        const uint64_t m = __ballot(mid == L);
+        if (mid == L)
+          place[L][wave][have[L] + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                       __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] =
+              (uint8_t)(p0 + lane);
+        have[L] += __builtin_popcountll(m);
+      }
+    }
+    if (lane < 4) tokens[lane][wave] = lane == 0 ? have[0] : lane == 1 ? have[1] : lane == 2 ? have[2] : have[3];
   }
-  reinterpret_cast<float4*>(out + s * 256)[lane] = make_float4(c0.x, c0.y, c1.x, c1.y);
+  __syncthreads();
+
+  const int L = wave >> 1, g = lane >> 4;
+  u32x4 w2[2][2][3];
+  load_w2(params, L, lane, w2);
+  for (int s = wave & 1; s < n_own; s += 2) {
+    const int n = tokens[L][s];
+    float re[8], im[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) re[i] = im[i] = 0.f;
+    for (int t = 0; t < n; t += 16) {
+      const int i = t + (lane & 15);
+      const bool valid = i < n;
+      const int p = place[L][s][valid ? i : 0];
+      float sn[8], cs[8];
+      const uint8_t* let = &letters[s][p];
+      token_phases(params, net, w2, L, let, flank_fragment(let, g), p, Nf, inv_n, turn, lane, sn, cs);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        re[q] += valid ? cs[q] : 0.f;
+        im[q] += valid ? sn[q] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      re[q] = row_sum(re[q]);
+      im[q] = row_sum(im[q]);
+    }
+    if ((lane & 15) == 0) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        *reinterpret_cast<float2*>(&c[s][((16 * (q >> 2) + 4 * g + (q & 3)) * 4 + L) * 2]) =
+            make_float2(re[q], im[q]);
+    }
+  }
+  __syncthreads();
+  if (wave < n_own)
+    reinterpret_cast<float4*>(out + (first + wave) * 256)[lane] =
+        *reinterpret_cast<const float4*>(&c[wave][4 * lane]);
+  if (F != nullptr && 2 * wave + 1 < n_own) {
+    const float f = fidelity(*reinterpret_cast<const float4*>(&c[2 * wave][4 * lane]),
+                             *reinterpret_cast<const float4*>(&c[2 * wave + 1][4 * lane]));
+    if (lane == 0) F[(first >> 1) + wave] = f;
+  }
 }
 
 // The plain encoding (§2.2, s = 1) of whole strings in FP32, for comparison:
@@ -178,149 +414,139 @@ __global__ __launch_bounds__(256) void pair_fidelity_kernel(const float* __restr
   const int lane = threadIdx.x & 63;
   const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (i >= n_pairs) return;
-  float4 a = reinterpret_cast<const float4*>(ca + i * stride)[lane];
-  float4 b = reinterpret_cast<const float4*>(cb + i * stride)[lane];
-  // z = sum conj(a) b
-  float zr = wave_sum(a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w);
-  float zi = wave_sum(a.x * b.y - a.y * b.x + a.z * b.w - a.w * b.z);
-  float A = wave_sum(a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w);
-  float B = wave_sum(b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w);
-  if (lane == 0) F[i] = (A > 0.f && B > 0.f) ? (zr * zr + zi * zi) / (A * B) : 0.f;
+  const float f = fidelity(reinterpret_cast<const float4*>(ca + i * stride)[lane],
+                           reinterpret_cast<const float4*>(cb + i * stride)[lane]);
+  if (lane == 0) F[i] = f;
 }
 
-// Ranking loss, pass 1: thread (i, part) sums over its eighth of the j's the
-// terms of pair (i, j): loss softplus(z) and count for d_i < d_j (z = -(F_i -
-// F_j) / tau), and the unscaled dLoss/dF_i contributions -sigma(z_ij) (d_i <
-// d_j) and +sigma(z_ji) (d_j < d_i).  The eight parts are summed in a fixed
-// order; per-i results go to g, lossv, cntv.
-constexpr int kRankI = 32, kRankParts = 8;
+// Ranking loss: per pair i, over all j, the loss terms softplus(z) and count
+// for d_i < d_j (z = -(F_i - F_j) / tau), and the unscaled dLoss/dF_i
+// contributions -sigma(z_ij) (d_i < d_j) and +sigma(z_ji) (d_j < d_i), with
+// e = exp(-|z|): softplus = max(z, 0) + log1p(e), sigma = 1 / (1 + e) or
+// e / (1 + e).  A block of four wavefronts per i (79 us for 1,024 pairs with a
+// lane per i and an eighth of the j's, 14 us with a wavefront per i): a lane
+// adds its j's in order, the lanes in wave_sum's fixed order, the wavefronts in
+// theirs.  A training step's count (step, if not null) advances here, before
+// the kernel that uses it.
+constexpr int kRankWaves = 4;
 
-__global__ __launch_bounds__(kRankI * kRankParts) void ranking_pairs_kernel(
+__global__ __launch_bounds__(64 * kRankWaves) void ranking_kernel(
     const float* __restrict__ F, const int32_t* __restrict__ ld, int32_t n,
-    float* __restrict__ g_out, float* __restrict__ loss_out, int32_t* __restrict__ cnt_out) {
-  __shared__ float sF[RM_LEARNED_MAX_PAIRS];
-  __shared__ int sL[RM_LEARNED_MAX_PAIRS];
-  __shared__ float rg[kRankParts][kRankI], rl[kRankParts][kRankI];
-  __shared__ int rc[kRankParts][kRankI];
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    sF[i] = F[i];
-    sL[i] = ld[i];
-  }
-  __syncthreads();
-  const int ti = threadIdx.x % kRankI, part = threadIdx.x / kRankI;
-  const int i = blockIdx.x * kRankI + ti;
-  float g = 0.f, l = 0.f;
-  int cnt = 0;
-  if (i < n) {
-    const float Fi = sF[i];
-    const int Li = sL[i];
-    const int per = (n + kRankParts - 1) / kRankParts;
-    const int j0 = part * per, j1 = min(n, j0 + per);
-    for (int j = j0; j < j1; ++j) {
-      const int Lj = sL[j];
-      if (Li < Lj) {  // want F_i > F_j
-        const float z = -(Fi - sF[j]) / kTau;
-        l += z > 20.f ? z : log1pf(expf(z));
-        ++cnt;
-        g -= 1.f / (1.f + expf(-z));
-      } else if (Lj < Li) {
-        const float z = -(sF[j] - Fi) / kTau;
-        g += 1.f / (1.f + expf(-z));
-      }
+    float* __restrict__ g_out, float* __restrict__ loss_out, int32_t* __restrict__ cnt_out,
+    float* __restrict__ step) {
+  __shared__ float part[3][kRankWaves];
+  const int i = blockIdx.x;
+  if (step != nullptr && i == 0 && threadIdx.x == 0) *step += 1.f;
+  const float Fi = F[i];
+  const int Li = ld[i];
+  float g = 0.f, l = 0.f, cnt = 0.f;
+  for (int j = threadIdx.x; j < n; j += 64 * kRankWaves) {
+    const int Lj = ld[j];
+    if (Li == Lj) continue;
+    const bool lower = Li < Lj;  // want F_i > F_j
+    const float z = (lower ? F[j] - Fi : Fi - F[j]) * kInvTau;
+    const float e = expf(-fabsf(z));
+    const float sigma = (z > 0.f ? 1.f : e) / (1.f + e);
+    if (lower) {
+      l += fmaxf(z, 0.f) + log1pf(e);
+      cnt += 1.f;
+      g -= sigma;
+    } else {
+      g += sigma;
     }
   }
-  rg[part][ti] = g;
-  rl[part][ti] = l;
-  rc[part][ti] = cnt;
+  g = wave_sum(g);
+  l = wave_sum(l);
+  cnt = wave_sum(cnt);  // at most 1,024: exact
+  if ((threadIdx.x & 63) == 0) {
+    part[0][threadIdx.x >> 6] = g;
+    part[1][threadIdx.x >> 6] = l;
+    part[2][threadIdx.x >> 6] = cnt;
+  }
   __syncthreads();
-  if (part == 0 && i < n) {
-    for (int q = 1; q < kRankParts; ++q) {
-      g += rg[q][ti];
-      l += rl[q][ti];
-      cnt += rc[q][ti];
-    }
-    g_out[i] = g;
-    loss_out[i] = l;
-    cnt_out[i] = cnt;
+  if (threadIdx.x == 0) {
+    g_out[i] = (part[0][0] + part[0][1]) + (part[0][2] + part[0][3]);
+    loss_out[i] = (part[1][0] + part[1][1]) + (part[1][2] + part[1][3]);
+    cnt_out[i] = (int)(part[2][0] + part[2][1] + part[2][2] + part[2][3]);
   }
 }
 
-// Ranking loss, pass 2 (one block): the loss is the sum of the terms over the
-// number of ordered pairs; dLoss/dF_i = g_i / (tau * count).
-__global__ __launch_bounds__(1024) void ranking_finalize_kernel(
-    float* __restrict__ g, const float* __restrict__ lossv, const int32_t* __restrict__ cntv,
-    int32_t n, float* __restrict__ loss) {
-  __shared__ float sl[1024];
-  __shared__ int sc[1024];
-  const int t = threadIdx.x;
-  sl[t] = t < n ? lossv[t] : 0.f;
-  sc[t] = t < n ? cntv[t] : 0;
-  __syncthreads();
-  for (int d = 512; d > 0; d >>= 1) {  // fixed-order tree
-    if (t < d) {
-      sl[t] += sl[t + d];
-      sc[t] += sc[t + d];
-    }
-    __syncthreads();
-  }
-  const float C = (float)sc[0];
-  if (t == 0) *loss = sc[0] > 0 ? sl[0] / C : 0.f;
-  const float scale = sc[0] > 0 ? 1.f / (kTau * C) : 0.f;
-  if (t < n) g[t] *= scale;
-}
-
-// Backward: per string, dLoss/dc = dLoss/dF * dF/dc, then through the tokens
-// and the network.  Deterministic: every lane accumulates its own share of the
-// gradient (lane (k, hh): dW2 rows L*32+k, columns 32hh..32hh+31, and db2 for
-// hh = 0, in registers; lane j: dW1 column j in the wavefront's LDS slice and
-// db1 in a register), the wavefronts of a block are summed in a fixed order
+// Backward: per string, dLoss/dc = dLoss/dF * dF/dc (dLoss/dF_i = g_i over tau
+// and the count of ordered pairs), then through the tokens and the network.
+// The block's tokens are sorted by middle letter over all its strings (little
+// of a 16-token tile is padding), two wavefronts per letter taking every other
+// tile:
+//   the forward up to the phases, tokens as columns;
+//   d delta_k = -G_r sin + G_i cos, in the layer-2 accumulator layout;
+//   dH [16 x 64] = dD [16 x 32] W2_L [32 x 64] in FP32 MFMAs, whose A operand
+//     is d delta as it lies, masked by H [16 x 64] = relu(X W1^T): layer 1 once
+//     more with its operands swapped.  Both leave four tokens of one hidden
+//     unit in a lane, so they are B operands of the sums over tokens:
+//   dW2_L [32 x 64] += dD^T H in FP32 MFMAs (d delta goes through LDS once to
+//     become the A operand) and dW1^T [32 x 64] += X^T dP as three bf16 MFMAs
+//     (one-hot X, dP split exactly).
+// A wavefront keeps its letter's dW2 block, a dW1 and the bias sums in
+// registers over all its tiles.  The wavefronts are added in a fixed order
 // through LDS, and the per-block partials in block order by the reduction
-// kernel.
-// Strings are taken in a grid-stride loop.
-constexpr int kRedW1 = 0, kRedB1 = kHid * 33, kRedW2 = kRedB1 + kHid, kRedB2 = kRedW2 + kOut * 65;
-constexpr int kRedSize = kRedB2 + kOut;  // padded rows: conflict-free LDS writes
-static_assert(kRedSize * sizeof(float) <= sizeof(Weights), "reduction buffer reuses the weights");
+// kernel: deterministic.  Bound by issue: the FP32 MFMAs (2,048 cycles a tile)
+// and the VALU work of phases and splits (about 2,400) hardly overlap.
+constexpr int kRowD = 48;  // floats of a token's d delta in LDS (conflict-free columns)
+struct Sums {
+  float w1[kWaves][kIn * kHid];  // dW1^T of every wavefront
+  float w2[4][32 * kHid];        // dW2 of a letter's second wavefront
+  float b1[kWaves][kHid];
+  float b2[kWaves][32];
+};
 
 __global__ __launch_bounds__(64 * kWaves, 2) void learned_backward_kernel(
-    const float* __restrict__ params, Strings st, int32_t n_pairs, int N,
-    const float* __restrict__ c, const float* __restrict__ dF, float* __restrict__ partial) {
+    const float* __restrict__ params, Strings st, int32_t n_pairs, int per, float Nf, float inv_n,
+    float turn, const float* __restrict__ c, const float* __restrict__ rank_g,
+    const int32_t* __restrict__ cnt, float* __restrict__ partial) {
+  __shared__ Net net;
+  __shared__ uint8_t letters[kStrings][kMaxLen + 8];
+  __shared__ uint16_t list[4][kStrings * kMaxTok];  // string << 8 | location
+  __shared__ int tokens[4][kStrings];
+  __shared__ __align__(16) float2 G[kStrings][4][32];
   __shared__ union {
-    Weights w;
-    float red[kRedSize];
+    struct {
+      f32x4 w2t[4][2][4][64];  // W2_L's rows as B fragments of dH
+      float d[kWaves][16 * kRowD];
+    } run;
+    Sums sum;
   } u;
-  __shared__ uint8_t letters[kWaves][kMaxLen];
-  __shared__ float hbuf[kWaves][kHid];
-  __shared__ float dbuf[kWaves][32];         // dLoss/d delta of the current token
-  __shared__ float gw1[kWaves][kIn * kHid];  // dW1 transposed, [input][hidden]
-  load_weights(u.w, params);
-  for (int i = threadIdx.x; i < kWaves * kIn * kHid; i += blockDim.x) (&gw1[0][0])[i] = 0.f;
-  __syncthreads();
-  const Weights& w = u.w;
-
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int k = lane >> 1, hh = lane & 1;
-  float aw2[4][32], ab2[4], ab1 = 0.f;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t first = (int64_t)blockIdx.x * per;
+  const int n_own = (int)min<int64_t>(per, 2 * (int64_t)n_pairs - first);
+  load_net(net, params);
+  // hidden units 16 cb + lane % 16, K entry j = factor 16 (j / 4) + 4 (lane / 16) + j % 4
+  for (int i = wave; i < 16; i += kWaves) {
+    const int L = i >> 2, cb = i & 3;
+    const float* src = params + kW2 + (L * 32 + 4 * (lane >> 4)) * kHid + 16 * cb + (lane & 15);
+    float x[8];
 #pragma unroll
-  for (int L = 0; L < 4; ++L) {
-    ab2[L] = 0.f;
-#pragma unroll
-    for (int i = 0; i < 32; ++i) aw2[L][i] = 0.f;
+    for (int j = 0; j < 8; ++j) x[j] = src[(16 * (j >> 2) + (j & 3)) * kHid];
+    u.run.w2t[L][0][cb][lane] = f32x4{x[0], x[1], x[2], x[3]};
+    u.run.w2t[L][1][cb][lane] = f32x4{x[4], x[5], x[6], x[7]};
   }
-
-  for (int64_t s = (int64_t)blockIdx.x * kWaves + wave; s < 2 * (int64_t)n_pairs;
-       s += (int64_t)gridDim.x * kWaves) {
-    const int64_t pr = s >> 1;
-    const bool is_b = s & 1;
+  int n = 0;
+  if (wave < n_own) {
+    const int64_t pr = (first + wave) >> 1;
+    const bool is_b = wave & 1;  // `per` is even
     // dF/dc for this side: F = |z|^2/(AB), z = <a|b>
-    float4 a = reinterpret_cast<const float4*>(c + (2 * pr) * 256)[lane];
-    float4 b = reinterpret_cast<const float4*>(c + (2 * pr + 1) * 256)[lane];
-    float zr = wave_sum(a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w);
-    float zi = wave_sum(a.x * b.y - a.y * b.x + a.z * b.w - a.w * b.z);
-    float A = wave_sum(a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w);
-    float B = wave_sum(b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w);
+    const float4 a = reinterpret_cast<const float4*>(c + (2 * pr) * 256)[lane];
+    const float4 b = reinterpret_cast<const float4*>(c + (2 * pr + 1) * 256)[lane];
+    const float zr = wave_sum(a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w);
+    const float zi = wave_sum(a.x * b.y - a.y * b.x + a.z * b.w - a.w * b.z);
+    const float A = wave_sum(a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w);
+    const float B = wave_sum(b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w);
     float g0r = 0.f, g0i = 0.f, g1r = 0.f, g1i = 0.f;
-    if (A > 0.f && B > 0.f) {
-      const float F = (zr * zr + zi * zi) / (A * B), d = dF[pr], AB = A * B;
+    int pairs = 0;  // ordered pairs of the batch: every wavefront adds them up
+    for (int i = lane; i < n_pairs; i += 64) pairs += cnt[i];
+    pairs = (int)wave_sum((float)pairs);  // at most 2^19: exact
+    if (A > 0.f && B > 0.f && pairs > 0) {
+      const float d = rank_g[pr] * (kInvTau / (float)pairs);
+      const float F = (zr * zr + zi * zi) / (A * B), AB = A * B;
       if (!is_b) {  // G_a = 2 conj(z) b / (AB) - 2 F a / A
         g0r = d * (2.f * (zr * b.x + zi * b.y) / AB - 2.f * F * a.x / A);
         g0i = d * (2.f * (zr * b.y - zi * b.x) / AB - 2.f * F * a.y / A);
@@ -334,99 +560,231 @@ __global__ __launch_bounds__(64 * kWaves, 2) void learned_backward_kernel(
       }
     }
     // lane (k, hh) holds G of components (k, 2hh) and (k, 2hh+1)
-    const int n = load_string(letters[wave], st, s, lane);
-    for (int p = 0; p + 9 <= n; ++p) {
-      Token t = token_forward(w, letters[wave], p, N, hbuf[wave], lane);
-      const int Lm = __builtin_amdgcn_readfirstlane(t.mid);
-      if (Lm >= 4) continue;  // uniform: no token here
-      // d delta_k = Re(conj(G) i e^{i phi}) = -Gr sin + Gi cos, G of component
-      // (k, Lm) from lane (k, Lm / 2)
-      const int src = 2 * k + (Lm >> 1);
-      const float r0 = __shfl(g0r, src, 64), i0 = __shfl(g0i, src, 64);
-      const float r1 = __shfl(g1r, src, 64), i1 = __shfl(g1i, src, 64);
-      const float Gr = (Lm & 1) ? r1 : r0, Gi = (Lm & 1) ? i1 : i0;
-      const float dd = -Gr * t.s + Gi * t.c;
-      if (hh == 0) dbuf[wave][k] = dd;
-      // dW2[L*32+k][32hh+i] += dd * h_(32hh+i); h of this token is still in hbuf
-      const float* hv = &hbuf[wave][32 * hh];
-      const float db = hh == 0 ? dd : 0.f;
-      switch (Lm) {
-#define RM_ACC_W2(L)                                                      \
-  case L:                                                                 \
-    _Pragma("unroll") for (int i = 0; i < 32; i += 4) {                   \
-      const float4 v = *reinterpret_cast<const float4*>(hv + i);          \
-      aw2[L][i] += dd * v.x;                                              \
-      aw2[L][i + 1] += dd * v.y;                                          \
-      aw2[L][i + 2] += dd * v.z;                                          \
-      aw2[L][i + 3] += dd * v.w;                                          \
-    }                                                                     \
-    ab2[L] += db;                                                         \
-    break;
-        RM_ACC_W2(0)
-        RM_ACC_W2(1)
-        RM_ACC_W2(2)
-        RM_ACC_W2(3)
-#undef RM_ACC_W2
-      }
-      __builtin_amdgcn_wave_barrier();
-      // dh_j = sum_k W2[L*32+k][j] d delta_k  (lane j)
-      float dh = 0.f;
-      const float* wcol = &w.w2[(Lm * 32) * kW2Stride + lane];
-#pragma unroll 8
-      for (int kk = 0; kk < 32; ++kk) dh += wcol[kk * kW2Stride] * dbuf[wave][kk];
-      const float dpre = t.pre > 0.f ? dh : 0.f;
-      ab1 += dpre;
+    G[wave][2 * (lane & 1)][lane >> 1] = make_float2(g0r, g0i);
+    G[wave][2 * (lane & 1) + 1][lane >> 1] = make_float2(g1r, g1i);
+    n = load_string(letters[wave], st, first + wave, lane);
+    int have[4] = {0, 0, 0, 0};
+    for (int p0 = 0; p0 < n; p0 += 64) {
+      const int mid = p0 + lane < n ? (int)letters[wave][p0 + lane + 4] : 4;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int f = letters[wave][p + (i < 4 ? i : i + 1)];
-        if (f < 4) gw1[wave][(4 * i + f) * kHid + lane] += dpre;
-      }
-      __builtin_amdgcn_wave_barrier();  // dbuf and hbuf are rewritten by the next token
+      for (int L = 0; L < 4; ++L) have[L] += __builtin_popcountll(__ballot(mid == L));
     }
+    if (lane < 4) tokens[lane][wave] = lane == 0 ? have[0] : lane == 1 ? have[1] : lane == 2 ? have[2] : have[3];
   }
-  __syncthreads();  // every wavefront is done with the weights: reuse them
-  float* red = u.red;
-  for (int wv = 0; wv < kWaves; ++wv) {
-    if (wave == wv) {
-      const bool first = wv == 0;
+  __syncthreads();
+  if (wave < n_own) {
+    int at[4] = {0, 0, 0, 0};
+    for (int s = 0; s < wave; ++s)
+#pragma unroll
+      for (int L = 0; L < 4; ++L) at[L] += tokens[L][s];
+    for (int p0 = 0; p0 < n; p0 += 64) {
+      const int mid = p0 + lane < n ? (int)letters[wave][p0 + lane + 4] : 4;
 #pragma unroll
       for (int L = 0; L < 4; ++L) {
-        float* row = &red[kRedW2 + (L * 32 + k) * 65 + 32 * hh];
-#pragma unroll
-        for (int i = 0; i < 32; ++i) row[i] = (first ? 0.f : row[i]) + aw2[L][i];
-        if (hh == 0) {
-          float& b2 = red[kRedB2 + L * 32 + k];
-          b2 = (first ? 0.f : b2) + ab2[L];
-        }
+        const uint64_t m = __ballot(mid == L);
+        if (mid == L)
+          list[L][at[L] + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                              __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] =
+              (uint16_t)(wave << 8 | (p0 + lane));
+        at[L] += __builtin_popcountll(m);
       }
-      float* col = &red[kRedW1 + lane * 33];
-#pragma unroll 8
-      for (int i = 0; i < kIn; ++i) col[i] = (first ? 0.f : col[i]) + gw1[wave][i * kHid + lane];
-      red[kRedB1 + lane] = (first ? 0.f : red[kRedB1 + lane]) + ab1;
     }
-    __syncthreads();
   }
+  __syncthreads();
+
+  const int L = wave >> 1, g = lane >> 4, col = lane & 15;
+  int n_tok = 0;
+  for (int s = 0; s < n_own; ++s) n_tok += tokens[L][s];
+  u32x4 w2[2][2][3];
+  load_w2(params, L, lane, w2);
+  f32x4 gw2[2][4], gw1[2][4], gb2[2];
+  float gb1[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    gb2[i] = f32x4{};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) gw2[i][j] = gw1[i][j] = f32x4{};
+  }
+  float* dbuf = u.run.d[wave];
+
+  for (int t = 16 * (wave & 1); t < n_tok; t += 32) {
+    const bool valid = t + col < n_tok;
+    const float live = valid ? 1.f : 0.f;  // a padding column repeats a token, with no weight
+    const int e = list[L][valid ? t + col : t];
+    const int s = e >> 8, p = e & 255;
+    const u32x4 x = flank_fragment(&letters[s][p], g);
+    float dd[8];
+    {
+      float sn[8], cs[8];
+      token_phases(params, net, w2, L, &letters[s][p], x, p, Nf, inv_n, turn, lane, sn, cs);
+#pragma unroll
+      for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float2 Gk = G[s][L][16 * ob + 4 * g + v];
+          const float d = live * (Gk.y * cs[4 * ob + v] - Gk.x * sn[4 * ob + v]);
+          dd[4 * ob + v] = d;
+          gb2[ob][v] += d;
+        }
+    }
+#pragma unroll
+    for (int ob = 0; ob < 2; ++ob)
+      *reinterpret_cast<f32x4*>(&dbuf[col * kRowD + 16 * ob + 4 * g]) =
+          f32x4{dd[4 * ob], dd[4 * ob + 1], dd[4 * ob + 2], dd[4 * ob + 3]};
+    __builtin_amdgcn_wave_barrier();
+    // d delta of tokens 4 g + j, factor 16 ob + col
+    f32x4 df[2];
+#pragma unroll
+    for (int ob = 0; ob < 2; ++ob) {
+      f32x4 d;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) d[j] = dbuf[(4 * g + j) * kRowD + 16 * ob + col];
+      df[ob] = d;
+    }
+    // one-hot of tokens 4 g + j, input 16 rb + col = 4 i + letter of flank i
+    s16x4 hot[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int ej = list[L][min(t + 4 * g + j, n_tok - 1)];  // past the end: dP is zero
+      const uint8_t* let = &letters[ej >> 8][ej & 255];
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        const int i = 4 * rb + (col >> 2);
+        hot[rb][j] = let[i + (i > 3)] == (col & 3) ? (short)0x3F80 : (short)0;
+      }
+    }
+    f32x4 hid[4];  // tokens 4 g + v, hidden units 16 cb + col
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+      const float b1 = net.b1[16 * cb + col];
+      hid[cb] = f32x4{b1, b1, b1, b1};
+#pragma unroll
+      for (int q = 2; q >= 0; --q) hid[cb] = mfma32(x, net.w1[q][cb][lane], hid[cb]);
+    }
+    settle(params, hid, [&](int i) { return 16 * (i >> 2) + col; },
+           [&](int i) {
+             const int ei = list[L][min(t + 4 * g + (i & 3), n_tok - 1)];
+             return &letters[ei >> 8][ei & 255];
+           });
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb) {
+      f32x4 h = hid[cb];
+      f32x4 dh{};
+      const f32x4 wa = u.run.w2t[L][0][cb][lane], wb = u.run.w2t[L][1][cb][lane];
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        dh = __builtin_amdgcn_mfma_f32_16x16x4f32(dd[j], j < 4 ? wa[j] : wb[j - 4], dh, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        dh[v] = h[v] > 0.f ? dh[v] : 0.f;
+        gb1[cb] += dh[v];
+        h[v] = relu(h[v]);
+      }
+      s16x4 pp[3];
+      split4(dh, pp);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int ob = 0; ob < 2; ++ob)
+          gw2[ob][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(df[ob][j], h[j], gw2[ob][cb], 0, 0, 0);
+#pragma unroll
+      for (int q = 2; q >= 0; --q)
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+          gw1[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(hot[rb], pp[q], gw1[rb][cb], 0, 0, 0);
+    }
+    __builtin_amdgcn_wave_barrier();  // dbuf is rewritten by the next tile
+  }
+
+  __syncthreads();  // every wavefront is done with the run's LDS
+  Sums& sum = u.sum;
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        sum.w1[wave][(16 * rb + 4 * g + v) * kHid + 16 * cb + col] = gw1[rb][cb][v];
+        if (wave & 1) sum.w2[L][(16 * rb + 4 * g + v) * kHid + 16 * cb + col] = gw2[rb][cb][v];
+      }
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb) {  // the four lane groups hold four tokens each
+    float b = gb1[cb];
+    b += __shfl_xor(b, 16, 64);
+    b += __shfl_xor(b, 32, 64);
+    if (g == 0) sum.b1[wave][16 * cb + col] = b;
+  }
+#pragma unroll
+  for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float b = row_sum(gb2[ob][v]);
+      if (col == 0) sum.b2[wave][16 * ob + 4 * g + v] = b;
+    }
+  __syncthreads();
   // partial gradient of this block, parameter order
   float* out = partial + (int64_t)blockIdx.x * kParams;
-  for (int i = threadIdx.x; i < kHid * kIn; i += blockDim.x)
-    out[kW1 + i] = red[kRedW1 + (i / kIn) * 33 + (i % kIn)];
-  for (int i = threadIdx.x; i < kHid; i += blockDim.x) out[kB1 + i] = red[kRedB1 + i];
-  for (int i = threadIdx.x; i < kOut * kHid; i += blockDim.x)
-    out[kW2 + i] = red[kRedW2 + (i / kHid) * 65 + (i % kHid)];
-  for (int i = threadIdx.x; i < kOut; i += blockDim.x) out[kB2 + i] = red[kRedB2 + i];
+  if (!(wave & 1)) {
+#pragma unroll
+    for (int ob = 0; ob < 2; ++ob)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = 16 * ob + 4 * g + v, j = 16 * cb + col;
+          out[kW2 + (L * 32 + r) * kHid + j] = gw2[ob][cb][v] + sum.w2[L][r * kHid + j];
+        }
+  }
+  for (int i = threadIdx.x; i < kIn * kHid; i += blockDim.x) {
+    float w = sum.w1[0][i];
+#pragma unroll
+    for (int q = 1; q < kWaves; ++q) w += sum.w1[q][i];
+    out[kW1 + (i % kHid) * kIn + i / kHid] = w;
+  }
+  if (threadIdx.x < kHid) {
+    float b = sum.b1[0][threadIdx.x];
+#pragma unroll
+    for (int q = 1; q < kWaves; ++q) b += sum.b1[q][threadIdx.x];
+    out[kB1 + threadIdx.x] = b;
+  } else if (threadIdx.x < kHid + kOut) {
+    const int i = threadIdx.x - kHid;
+    out[kB2 + i] = sum.b2[i / 32 * 2][i % 32] + sum.b2[i / 32 * 2 + 1][i % 32];
+  }
 }
 
 // Sum of the per-block partial gradients (block: 64 parameters x 16 subsets
 // of the partials, summed in a fixed order); then either the gradient is
 // written (grad != nullptr) or an Adam step is applied to state = [params | m
-// | v | t].
+// | v | t].  One more block sums the loss terms, over the number of ordered
+// pairs.  The step count t is advanced by the ranking of the same step.
 constexpr int kRedParams = 64, kRedParts = 16;
+constexpr int kRedBlocks = (kParams + kRedParams - 1) / kRedParams;
 
 __global__ __launch_bounds__(kRedParams * kRedParts) void reduce_adam_kernel(
-    const float* __restrict__ partial, int n_blocks, float* __restrict__ grad,
-    float* __restrict__ state, float lr) {
+    const float* __restrict__ partial, int n_blocks, const float* __restrict__ lossv,
+    const int32_t* __restrict__ cnt, int32_t n, float* __restrict__ loss,
+    float* __restrict__ grad, float* __restrict__ state, float lr) {
   __shared__ float red[kRedParts][kRedParams];
   const int tp = threadIdx.x % kRedParams, q = threadIdx.x / kRedParams;
+  if (blockIdx.x == kRedBlocks) {
+    const bool has = (int)threadIdx.x < n;
+    const float l = wave_sum(has ? lossv[threadIdx.x] : 0.f);
+    const float c = wave_sum(has ? (float)cnt[threadIdx.x] : 0.f);
+    if (tp == 0) {
+      red[0][q] = l;
+      red[1][q] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      float sum = red[0][0], pairs = red[1][0];
+      for (int r = 1; r < kRedParts; ++r) {
+        sum += red[0][r];
+        pairs += red[1][r];
+      }
+      *loss = pairs > 0.f ? sum / pairs : 0.f;
+    }
+    return;
+  }
   const int i = blockIdx.x * kRedParams + tp;
   float g = 0.f;
   if (i < kParams) {
@@ -452,7 +810,7 @@ __global__ __launch_bounds__(kRedParams * kRedParts) void reduce_adam_kernel(
     return;
   }
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const float t = state[3 * kParams] + 1.f;  // the step count is advanced by a separate kernel
+  const float t = state[3 * kParams];
   float m = b1 * state[kParams + i] + (1.f - b1) * g;
   float v = b2 * state[2 * kParams + i] + (1.f - b2) * g * g;
   state[kParams + i] = m;
@@ -462,15 +820,25 @@ __global__ __launch_bounds__(kRedParams * kRedParts) void reduce_adam_kernel(
   state[i] -= lr * mh / (sqrtf(vh) + eps);
 }
 
-__global__ void advance_step_kernel(float* __restrict__ state) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) state[3 * kParams] += 1.f;
-}
+static_assert(kRedParams == 64 && RM_LEARNED_MAX_PAIRS <= kRedParams * kRedParts,
+              "the loss block's layout");
+
+// Strings per block: a block per CU from 1,024 pairs on, two pairs at least.
+int strings_per_block(int64_t n_strings) { return n_strings > 1024 ? kStrings : kStrings / 2; }
+
+// The nominal length as the phases use it: a position's part of a turn in
+// quarter turns.
+struct Nominal {
+  float n, inv, turn;
+  explicit Nominal(int N)
+      : n((float)N), inv((float)(1.0 / N)), turn((float)(4.0 / N)) {}
+};
 
 }  // namespace
 
 size_t learned_workspace_bytes(int32_t n_pairs) {
   int64_t strings = 2 * (int64_t)n_pairs;
-  int64_t blocks = (strings + kWaves - 1) / kWaves;
+  int64_t blocks = (strings + 3) / 4;              // at least the blocks of a step
   size_t bytes = 0;
   bytes += (size_t)strings * 256 * sizeof(float);  // encodings
   bytes += (size_t)n_pairs * sizeof(float) * 4;    // F, dF, per-i loss, per-i count
@@ -486,9 +854,12 @@ hipError_t launch_learned_encode(const float* params, const uint8_t* seq, const 
                        dim3(256), 0, s, seq, off, n_strings, N, out);
     return hipGetLastError();
   }
-  unsigned blocks = (unsigned)(((int64_t)n_strings + kWaves - 1) / kWaves);
+  const int per = strings_per_block(n_strings);
+  const Nominal nom(N);
+  unsigned blocks = (unsigned)(((int64_t)n_strings + per - 1) / per);
   hipLaunchKernelGGL(learned_encode_kernel, dim3(blocks), dim3(64 * kWaves), 0, s, params,
-                     Strings{seq, off, nullptr, nullptr}, n_strings, N, out);
+                     Strings{seq, off, nullptr, nullptr}, n_strings, per, nom.n, nom.inv, nom.turn,
+                     out, (float*)nullptr);
   return hipGetLastError();
 }
 
@@ -507,8 +878,10 @@ hipError_t launch_learned_step(float* state, float lr, const uint8_t* a, const i
                                int32_t n_pairs, int N, void* ws, float* grad_out,
                                float* loss_out, hipStream_t s) {
   const int64_t strings = 2 * (int64_t)n_pairs;
-  const unsigned blocks = (unsigned)((strings + kWaves - 1) / kWaves);
+  const int per = strings_per_block(strings);
+  const unsigned blocks = (unsigned)((strings + per - 1) / per);
   const Strings st{a, aoff, b, boff};
+  const Nominal nom(N);
   uint8_t* base = static_cast<uint8_t*>(ws);
   float* c = reinterpret_cast<float*>(base);
   float* F = c + strings * 256;
@@ -519,20 +892,14 @@ hipError_t launch_learned_step(float* state, float lr, const uint8_t* a, const i
   float* partial = reinterpret_cast<float*>(
       (reinterpret_cast<uintptr_t>(loss_ws + 64) + 255) / 256 * 256);
   hipLaunchKernelGGL(learned_encode_kernel, dim3(blocks), dim3(64 * kWaves), 0, s, state, st,
-                     (int32_t)strings, N, c);
-  hipLaunchKernelGGL(pair_fidelity_kernel, dim3((unsigned)((n_pairs + 3) / 4)), dim3(256), 0, s, c,
-                     c + 256, (int64_t)512, n_pairs, F);
-  hipLaunchKernelGGL(ranking_pairs_kernel, dim3((unsigned)((n_pairs + kRankI - 1) / kRankI)),
-                     dim3(kRankI * kRankParts), 0, s, F, ld, n_pairs, dF, lossv, cntv);
-  hipLaunchKernelGGL(ranking_finalize_kernel, dim3(1), dim3(1024), 0, s, dF, lossv, cntv, n_pairs,
-                     loss_out ? loss_out : loss_ws);
+                     (int32_t)strings, per, nom.n, nom.inv, nom.turn, c, F);
+  hipLaunchKernelGGL(ranking_kernel, dim3((unsigned)n_pairs), dim3(64 * kRankWaves), 0, s, F, ld,
+                     n_pairs, dF, lossv, cntv, grad_out ? nullptr : state + 3 * kParams);
   hipLaunchKernelGGL(learned_backward_kernel, dim3(blocks), dim3(64 * kWaves), 0, s, state, st,
-                     n_pairs, N, c, dF, partial);
-  hipLaunchKernelGGL(reduce_adam_kernel, dim3((kParams + kRedParams - 1) / kRedParams),
-                     dim3(kRedParams * kRedParts), 0, s, partial, (int)blocks, grad_out,
-                     grad_out ? nullptr : state, lr);
-  if (grad_out == nullptr)
-    hipLaunchKernelGGL(advance_step_kernel, dim3(1), dim3(64), 0, s, state);
+                     n_pairs, per, nom.n, nom.inv, nom.turn, c, dF, cntv, partial);
+  hipLaunchKernelGGL(reduce_adam_kernel, dim3(kRedBlocks + 1), dim3(kRedParams * kRedParts), 0, s,
+                     partial, (int)blocks, lossv, cntv, n_pairs, loss_out ? loss_out : loss_ws,
+                     grad_out, grad_out ? nullptr : state, lr);
   return hipGetLastError();
 }
 

@@ -21,6 +21,7 @@
 // directly from the letters in FP64 (the re-anchor), then rolled in FP32.
 // Each window is normalised (§2.3) and written in the index precision.
 #include <mutex>
+#include <type_traits>
 #include <unordered_map>
 
 #include "rm_bf16.h"
@@ -30,6 +31,8 @@
 namespace rm {
 
 namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct Row4 {
   float v[4];
@@ -168,11 +171,10 @@ struct Row3 {
   float v[3];
 };
 
-// The lane's three reals of the projected row of (u0, u1) (its two
-// components), and of the matching "Im" row (-Im y, Re y) of a read.
-__device__ __forceinline__ void letter_sum_rows(float2 u0, float2 u1, int h, Row3& re, Row3& im) {
-  const float2 s = make_float2(u0.x + u1.x, u0.y + u1.y);
-  const float2 d = make_float2(u0.x - u1.x, u0.y - u1.y);
+// The lane's three reals of the projected row of its two components, given as
+// their sum s and difference d, and of the matching "Im" row (-Im y, Re y) of a
+// read.
+__device__ __forceinline__ void letter_sum_rows(float2 s, float2 d, int h, Row3& re, Row3& im) {
   // the partner lane's values (lane ^ 1), by DPP quad_perm [1,0,3,2]
   const float2 sp = make_float2(dpp<0xB1>(s.x), dpp<0xB1>(s.y));
   const float2 dp = make_float2(dpp<0xB1>(d.x), dpp<0xB1>(d.y));
@@ -750,17 +752,19 @@ __global__ __launch_bounds__(256) void encode_reference_kernel(
 // norm below kDegenerateRel * N gives the zero vector) and store its two real
 // rows: 2r = (Re x, Im x) per component, 2r+1 = (-Im x, Re x).  A window row
 // (Re c, Im c) dotted with them gives Re and Im of sum conj(x) c.
+// X: the squared norm, summed over the wavefront.
 template <int PREC, bool RED = false>
-__device__ __forceinline__ void emit_head(float2 a0, float2 a1, int N, int64_t r, int lane,
+__device__ __forceinline__ void emit_head(float2 a0, float2 a1, float X, int N, int64_t r, int lane,
                                           void* __restrict__ emb, float* __restrict__ scale) {
-  const float X = wave_sum(a0.x * a0.x + a0.y * a0.y + a1.x * a1.x + a1.y * a1.y);
   const float inv = X < kDegenerateRel * N ? 0.f : 1.f / sqrtf(X);
   const float xr0 = a0.x * inv, xi0 = a0.y * inv;
   const float xr1 = a1.x * inv, xi1 = a1.y * inv;
   float s;
   if constexpr (RED) {  // the letter-sum form (a window's all-letters part is zero)
     Row3 re, im;
-    letter_sum_rows(make_float2(xr0, xi0), make_float2(xr1, xi1), lane & 1, re, im);
+    letter_sum_rows(make_float2(__builtin_fmaf(a0.x, inv, xr1), __builtin_fmaf(a0.y, inv, xi1)),
+                    make_float2(__builtin_fmaf(a0.x, inv, -xr1), __builtin_fmaf(a0.y, inv, -xi1)),
+                    lane & 1, re, im);
     s = store_row3<PREC>(emb, 2 * r, lane, re);
     store_row3<PREC>(emb, 2 * r + 1, lane, im);
   } else {
@@ -773,21 +777,113 @@ __device__ __forceinline__ void emit_head(float2 a0, float2 a1, int N, int64_t r
 }
 
 // Read heads (§3.1: the first N letters of each read): an FP32 direct sum of
-// the FP32 phase table over the head's letters, one wavefront per read.  A
-// read shorter than N is the zero vector.
-template <int PREC, bool RED>
+// the FP32 phase table over the head's letters.  A read shorter than N is the
+// zero vector.
+//
+// The sums of 4 RB reads are one product of one-hot rows (read, letter) with
+// the table [position][64 reals] on 16x16x4 FP32 MFMAs, which add their four
+// products one after another, each addition rounded to nearest: every
+// component is the FP32 sum over its letter's positions in their order, bit
+// for bit what a loop over the positions gives (a position of another letter
+// adds 0).  Wavefront w of the block holds the table's reals 16 w .. 16 w + 15
+// of 64 positions in registers, a chunk ahead; the reads' letters go through
+// LDS, stored so that one word of a lane holds its positions of four MFMAs.
+// A lane's accumulator holds one read's four letters of one real; the rows
+// are then normalised and stored with one wavefront per read (emit_head).
+//
+// Bound by the FP32 MFMAs (32 cycles per four positions of four reads and 16
+// reals; they hold the VALU, which normalises and stores).  100,000 reads of
+// 150 letters: 125 us, 425 us with one wavefront per read adding its positions
+// one after another; 350 reads of 6,400 letters 110 and 279 us.  RB = 8 reuses
+// each table value for 32 reads; fewer reads take RB = 1, whose longer grid
+// finishes sooner.
+constexpr int kHeadRow = 68;  // floats of a (read, letter) row in LDS, conflict-free
+
+template <int PREC, bool RED, int RB>
 __global__ __launch_bounds__(256) void encode_reads_kernel(
     const uint8_t* __restrict__ seq, const int64_t* __restrict__ off, int32_t n_reads, int N,
-    const float2* __restrict__ phase32, void* __restrict__ emb, float* __restrict__ scale) {
+    const float* __restrict__ tab, void* __restrict__ emb, float* __restrict__ scale) {
+  constexpr int READS = 4 * RB;
+  __shared__ uint32_t letters[2][READS][16];  // word 4 q + g, byte s: position 16 q + 4 s + g
+  __shared__ float mat[READS * 4 * kHeadRow];
   const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * (blockDim.x >> 6) +
-                    __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (r >= n_reads) return;
-  const int64_t start = off[r];
-  const int64_t len = off[r + 1] - start;
-  float2 a0 = make_float2(0.f, 0.f), a1 = make_float2(0.f, 0.f);
-  if (len >= N) direct_sum32(seq + start, N, phase32, lane, a0, a1);
-  emit_head<PREC, RED>(a0, a1, N, r, lane, emb, scale);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, col = lane & 15;
+  const int64_t r0 = (int64_t)blockIdx.x * READS;
+  // this wavefront stages the letters of reads wave, wave + 4, ...
+  const uint8_t* src[RB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i) {
+    const int64_t r = r0 + wave + 4 * i;
+    src[i] = nullptr;
+    if (r < n_reads) {
+      const int64_t start = off[r];
+      if (off[r + 1] - start >= N) src[i] = seq + start;
+    }
+  }
+  uint8_t next[RB];
+  float b[16];
+  auto fetch = [&](int pb) {  // letters and table values of positions pb .. pb + 63
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+      next[i] = src[i] != nullptr && pb + lane < N ? src[i][pb + lane] : (uint8_t)255;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int p = pb + 4 * u + g;
+      b[u] = p < N ? tab[(int64_t)p * 64 + 16 * wave + col] : 0.f;
+    }
+  };
+  const int byte = ((lane >> 4) * 4 + (lane & 3)) * 4 + ((lane >> 2) & 3);
+  auto stage = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+      reinterpret_cast<uint8_t*>(letters[buf][wave + 4 * i])[byte] = next[i];
+  };
+  f32x4 acc[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) acc[rb] = f32x4{};
+  fetch(0);
+  stage(0);
+  int buf = 0;
+  for (int pb = 0; pb < N; pb += 64, buf ^= 1) {
+    __syncthreads();
+    float t[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) t[u] = b[u];
+    if (pb + 64 < N) fetch(pb + 64);
+    const int nq = min(4, (N - pb + 15) >> 4);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (q >= nq) break;
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        const uint32_t w = letters[buf][4 * rb + (col >> 2)][4 * q + g];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          acc[rb] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+              ((w >> (8 * s)) & 0xff) == (uint32_t)(col & 3) ? 1.f : 0.f, t[4 * q + s], acc[rb],
+              0, 0, 0);
+      }
+    }
+    if (pb + 64 < N) stage(buf ^ 1);
+  }
+  // lane (g, col): read 4 rb + g, real 16 wave + col, letter v
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      mat[((4 * rb + g) * 4 + v) * kHeadRow + 16 * wave + col] = acc[rb][v];
+  __syncthreads();
+  const int k = lane >> 1, h = lane & 1;
+  for (int i = wave; i < READS; i += 4) {
+    if (r0 + i >= n_reads) break;
+    const float* row = &mat[(4 * i + 2 * h) * kHeadRow + 2 * k];
+    const float2 a0 = *reinterpret_cast<const float2*>(row);
+    const float2 a1 = *reinterpret_cast<const float2*>(row + kHeadRow);
+    const float X = wave_sum(__builtin_fmaf(
+        a1.y, a1.y, __builtin_fmaf(a1.x, a1.x, __builtin_fmaf(a0.y, a0.y, a0.x * a0.x))));
+    emit_head<PREC, RED>(a0, a1, X, N, r0 + i, lane, emb, scale);
+  }
 }
 
 // ---- learned token offsets -------------------------------------------------
@@ -959,7 +1055,8 @@ __global__ __launch_bounds__(256) void encode_reads_learned_kernel(
   const int64_t len = off[r + 1] - start;
   float2 a0 = make_float2(0.f, 0.f), a1 = make_float2(0.f, 0.f);
   if (len >= N) direct_sum_learned32(seq + start, N, delta + start * 32, phase32, lane, a0, a1);
-  emit_head<PREC>(a0, a1, N, r, lane, emb, scale);
+  emit_head<PREC>(a0, a1, wave_sum(a0.x * a0.x + a0.y * a0.y + a1.x * a1.x + a1.y * a1.y), N, r,
+                  lane, emb, scale);
 }
 
 // ---- token encodings (§2.1 s-mers, §2.6 compact versions) ----------------------
@@ -1041,7 +1138,8 @@ __global__ __launch_bounds__(256) void encode_reads_tokens_kernel(
   const int64_t len = off[r + 1] - start;
   float2 a0 = make_float2(0.f, 0.f), a1 = make_float2(0.f, 0.f);
   if (len >= N) direct_sum_tokens(seq + start, N - s + 1, s, table, phase32, m, k, c0, lane, a0, a1);
-  emit_head<PREC>(a0, a1, N, r, lane, emb, scale);
+  emit_head<PREC>(a0, a1, wave_sum(a0.x * a0.x + a0.y * a0.y + a1.x * a1.x + a1.y * a1.y), N, r,
+                  lane, emb, scale);
 }
 
 }  // namespace
@@ -1151,16 +1249,25 @@ hipError_t launch_encode_reference(const uint8_t* ref, int64_t W, const rm_param
 hipError_t launch_encode_reads(const rm_params& p, const float* phase32, const uint8_t* seq,
                                const int64_t* off, int32_t n_reads, void* emb, float* scale,
                                hipStream_t s) {
-  const int waves = 4;
-  int64_t blocks = ((int64_t)n_reads + waves - 1) / waves;
-  auto* ph = reinterpret_cast<const float2*>(phase32);
-  auto kern = p.reduced ? encode_reads_kernel<RM_FP32, true> : encode_reads_kernel<RM_FP32, false>;
-  if (p.precision == RM_FP16)
-    kern = p.reduced ? encode_reads_kernel<RM_FP16, true> : encode_reads_kernel<RM_FP16, false>;
-  else if (p.precision == RM_FP8_E4M3)
-    kern = p.reduced ? encode_reads_kernel<RM_FP8_E4M3, true> : encode_reads_kernel<RM_FP8_E4M3, false>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * waves), 0, s, seq, off, n_reads,
-                     p.window_len, ph, emb, scale);
+  // 32 reads per block once they give every CU two blocks, else 4: 16,000 reads
+  // of 150 letters take 26 against 29 us, 8,000 18 against 16 us, 350 of 6,400
+  // letters 401 against 110 us
+  const bool many = n_reads >= 16384;
+  auto launch = [&](auto prec, auto red) {
+    constexpr int P = decltype(prec)::value;
+    constexpr bool R = decltype(red)::value;
+    const int per = many ? 32 : 4;
+    hipLaunchKernelGGL((many ? encode_reads_kernel<P, R, 8> : encode_reads_kernel<P, R, 1>),
+                       dim3((unsigned)(((int64_t)n_reads + per - 1) / per)), dim3(256), 0, s, seq,
+                       off, n_reads, p.window_len, phase32, emb, scale);
+  };
+  auto by_form = [&](auto prec) {
+    if (p.reduced) launch(prec, std::true_type{});
+    else launch(prec, std::false_type{});
+  };
+  if (p.precision == RM_FP32) by_form(std::integral_constant<int, RM_FP32>{});
+  else if (p.precision == RM_FP16) by_form(std::integral_constant<int, RM_FP16>{});
+  else by_form(std::integral_constant<int, RM_FP8_E4M3>{});
   return hipGetLastError();
 }
 

@@ -9,8 +9,7 @@
 // accumulation give the FP32 direct sums up to the order of the additions.
 #pragma once
 
-#include <hip/hip_runtime.h>
-#include <stdint.h>
+#include "rm_internal.h"
 
 namespace rm {
 
@@ -40,15 +39,17 @@ __device__ __forceinline__ void split_bf16x3(float x, uint32_t& hi, uint32_t& mi
 __device__ __forceinline__ void stage_table_parts(const float* __restrict__ tab, int pb, int N,
                                                   u32x4 (*tparts)[2][8][32], int tid,
                                                   int nthreads) {
+#pragma unroll 2
   for (int f = tid; f < 512; f += nthreads) {
     const int c = f & 31, pg = (f >> 5) & 7, cb = f >> 8;
+    float x[8];  // loads without a branch, so that all are in flight together
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj)
+      x[jj] = tab[(int64_t)min(pb + 8 * pg + jj, N - 1) * 64 + cb * 32 + c];
     uint32_t hi[8], mid[8], lo[8];
 #pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
-      const int pos = pb + 8 * pg + jj;
-      const float x = pos < N ? tab[(int64_t)pos * 64 + cb * 32 + c] : 0.f;
-      split_bf16x3(x, hi[jj], mid[jj], lo[jj]);
-    }
+    for (int jj = 0; jj < 8; ++jj)
+      split_bf16x3(pb + 8 * pg + jj < N ? x[jj] : 0.f, hi[jj], mid[jj], lo[jj]);
     tparts[0][cb][pg][c] = u32x4{hi[0] | hi[1] << 16, hi[2] | hi[3] << 16, hi[4] | hi[5] << 16,
                                  hi[6] | hi[7] << 16};
     tparts[1][cb][pg][c] = u32x4{mid[0] | mid[1] << 16, mid[2] | mid[3] << 16,
@@ -69,6 +70,72 @@ __device__ __forceinline__ bf16x8 onehot_fragment(uint2 w, uint32_t onehot_tab) 
   const u32x4 av{__builtin_amdgcn_perm(0u, h0, 0x010c000cu), __builtin_amdgcn_perm(0u, h0, 0x030c020cu),
                  __builtin_amdgcn_perm(0u, h1, 0x010c000cu), __builtin_amdgcn_perm(0u, h1, 0x030c020cu)};
   return __builtin_bit_cast(bf16x8, av);
+}
+
+// ---- fidelities of eight strings from a row block of the product
+// Row 4 s + L of a block holds string s's sums for letter L, 64 reals (re, im per
+// factor); rows of kMatRow floats keep 16-byte reads aligned and the lanes'
+// rows in different banks.
+constexpr int kMatRow = 68;
+
+// F = |<x|c>|^2 / (X C) of the block's strings with the head x (rows `head`,
+// squared norm X; zero where X or C is below `lowest`), string s in lanes 8 s
+// .. 8 s + 7.  A lane takes four factors of its string: three sums of 32 reals in
+// registers, then three exchanges.  The additions are those of wave_sum over
+// lanes that hold a factor's two letter pairs each (pairs, then neighbours at
+// distance 2, 4, 8, 16 and 32), in its order, and every term is formed as it
+// was there, so F keeps its bits; a wavefront sum per string and per
+// term took 97 instructions a string, this takes about 19.
+__device__ __forceinline__ float strings_fidelity(const float (*mat)[kMatRow],
+                                                  const float (*head)[kMatRow], float X,
+                                                  float lowest, int lane) {
+  const int s = lane >> 3, c0 = 8 * (lane & 7);
+  float m[4][8], x[4][8];
+#pragma unroll
+  for (int L = 0; L < 4; ++L)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      *reinterpret_cast<float4*>(&m[L][4 * i]) =
+          *reinterpret_cast<const float4*>(&mat[4 * s + L][c0 + 4 * i]);
+      *reinterpret_cast<float4*>(&x[L][4 * i]) = *reinterpret_cast<const float4*>(&head[L][c0 + 4 * i]);
+    }
+  float C[4], R[4], I[4];
+#pragma unroll
+  for (int f = 0; f < 4; ++f) {
+    float c[2], r[2], q[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float ax = m[2 * h][2 * f], ay = m[2 * h][2 * f + 1];
+      const float bx = m[2 * h + 1][2 * f], by = m[2 * h + 1][2 * f + 1];
+      const float px = x[2 * h][2 * f], py = x[2 * h][2 * f + 1];
+      const float qx = x[2 * h + 1][2 * f], qy = x[2 * h + 1][2 * f + 1];
+      c[h] = __builtin_fmaf(by, by, __builtin_fmaf(bx, bx, __builtin_fmaf(ax, ax, ay * ay)));
+      r[h] = __builtin_fmaf(qy, by, __builtin_fmaf(qx, bx, __builtin_fmaf(px, ax, py * ay)));
+      q[h] = __builtin_fmaf(-qy, bx, __builtin_fmaf(qx, by, __builtin_fmaf(px, ay, -(py * ax))));
+    }
+    C[f] = c[0] + c[1];
+    R[f] = r[0] + r[1];
+    I[f] = q[0] + q[1];
+  }
+  auto total = [&](const float (&v)[4]) {
+    float t = (v[0] + v[1]) + (v[2] + v[3]);
+    t += dpp<0xB1>(t);   // quad_perm [1,0,3,2]
+    t += dpp<0x4E>(t);   // quad_perm [2,3,0,1]
+    t += dpp<0x141>(t);  // row_half_mirror
+    return t;
+  };
+  const float c = total(C), re = total(R), im = total(I);
+  return X < lowest || c < lowest ? 0.f : __builtin_fmaf(re, re, im * im) / (X * c);
+}
+
+// Squared norm of the head in rows `head`, summed like the strings' above, in
+// every lane.
+__device__ __forceinline__ float head_norm2(const float (*head)[kMatRow], int lane) {
+  const int k = lane >> 1, h = lane & 1;
+  const float2 a = *reinterpret_cast<const float2*>(&head[2 * h][2 * k]);
+  const float2 b = *reinterpret_cast<const float2*>(&head[2 * h + 1][2 * k]);
+  return wave_sum(__builtin_fmaf(
+      b.y, b.y, __builtin_fmaf(b.x, b.x, __builtin_fmaf(a.x, a.x, a.y * a.y))));
 }
 
 }  // namespace rm

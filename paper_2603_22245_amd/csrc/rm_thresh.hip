@@ -36,33 +36,48 @@ struct Words4 {
   uint32_t x, y, z, w;
 };
 
+// 32 x 32 -> 64-bit product as one instruction: low half x, high half y.  Both
+// halves of a product as v_mul_lo and v_mul_hi take a quarter-rate instruction
+// each.
+__device__ __forceinline__ uint2 wide_product(uint32_t a, uint32_t b) {
+  uint64_t p, carry;
+  asm("v_mad_u64_u32 %0, %1, %2, %3, 0" : "=v"(p), "=s"(carry) : "v"(b), "s"(a));
+  return make_uint2((uint32_t)p, (uint32_t)(p >> 32));
+}
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 // Philox4x32-10: ten rounds; a round multiplies words 0 and 2 by the two
 // round constants (64-bit products as high and low halves) and mixes them
 // with words 1 and 3 and the key; the key advances by the Weyl constants
-// between rounds.
+// between rounds.  Of the counter only word 3 (the step) differs between the
+// lanes of a wavefront, so the first round's products, word 0's in the second
+// and word 2's in the third are scalar.  Word 3 of the result is not formed.
 __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2,
                                                 uint32_t c3, uint32_t k0, uint32_t k1) {
+  constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     if (r) {
       k0 += 0x9E3779B9u;
       k1 += 0xBB67AE85u;
     }
-    const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-    const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
-    const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
+    const uint2 p0 = r < 2 ? make_uint2(M0 * c0, __umulhi(M0, c0)) : wide_product(M0, c0);
+    const uint2 p1 = r == 0 || r == 2 ? make_uint2(M1 * c2, __umulhi(M1, c2)) : wide_product(M1, c2);
+    const uint32_t n0 = xor3(p1.y, c1, k0), n2 = xor3(p0.y, c3, k1);
     c0 = n0;
-    c1 = lo1;
+    c1 = p1.x;
     c2 = n2;
-    c3 = lo0;
+    c3 = p0.x;
   }
-  return Words4{c0, c1, c2, c3};
+  return Words4{c0, c1, c2, 0u};
 }
 
-// Number of lanes below this one whose bit is set in `mask`.
-__device__ __forceinline__ int lanes_below(uint64_t mask) {
+// Number of lanes below this one whose bit is set in `mask`, plus `from`.
+__device__ __forceinline__ int lanes_below(uint64_t mask, int from = 0) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, (uint32_t)from));
 }
 
 __device__ __forceinline__ float fidelity32(float2 a0, float2 a1, float A, float2 b0, float2 b1,
@@ -157,6 +172,8 @@ __global__ __launch_bounds__(64 * kThrWaves) void window_thresholds_kernel(
 
 // ---- the regime's product pass
 
+constexpr int kDraw = 4;  // copies drawn together
+
 // The same thresholds with the strings' vectors from one MFMA product: each
 // wavefront writes the letters of its window (string 0) and of its copies
 // (strings 1..copies) into LDS, drawing the copies exactly as
@@ -164,70 +181,107 @@ __global__ __launch_bounds__(64 * kThrWaves) void window_thresholds_kernel(
 // (string, letter) rows of its four windows with the FP32 table split into
 // three bfloat16 parts (rm_bf16.h), in passes of 8 RB strings and chunks of
 // 64 positions, and each wavefront takes the fidelities of its copies with
-// its window from the product.  `np` is N rounded up to 64, `sp` the strings
+// its window from the product.  Bound by VALU issue, four fifths of it the
+// draws: 10^6 windows of 150 letters, 16 copies, in 11.8 ms (17.7 ms with two
+// quarter-rate multiplies per product, a letter from global memory per step,
+// masks by lane and a wavefront sum per copy and term).  `np` is N rounded up to 64, `sp` the strings
 // rounded up to whole passes; letters past a string's end are 4 (none).
 template <int RB>
-__global__ __launch_bounds__(64 * kThrWaves) void window_thresholds_mfma_kernel(
+__global__ __launch_bounds__(64 * kThrWaves, RB <= 3 ? 2 : 1) void window_thresholds_mfma_kernel(
     const uint8_t* __restrict__ ref, int64_t G, int64_t W, int N, int np, int stride,
     const float* __restrict__ tab, uint32_t T1, int copies, int sp, int rank, uint32_t seed,
     int max_steps, float* __restrict__ thr) {
   constexpr int SMAX = 8 * RB;
   typedef float f32x16 __attribute__((ext_vector_type(16)));
   extern __shared__ __attribute__((aligned(16))) uint8_t letters_dyn[];  // [waves][sp][np]
-  __shared__ u32x4 tparts[3][2][8][32];
-  __shared__ float mat_all[kThrWaves][32][2 * kM + 1];
+  __shared__ union {
+    u32x4 tparts[3][2][8][32];
+    float mat[kThrWaves][32][kMatRow];
+  } u;
+  __shared__ float head_all[kThrWaves][4][kMatRow];
+  auto& tparts = u.tparts;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t j = (int64_t)blockIdx.x * kThrWaves + wave;
   const bool active = j < W;  // inactive wavefronts still stage the table
   uint8_t* letters = letters_dyn + (size_t)wave * sp * np;
-  float(*mat)[2 * kM + 1] = mat_all[wave];
+  uint8_t* own = letters_dyn + (size_t)kThrWaves * sp * np + (size_t)wave * (np + 64);
+  float(*mat)[kMatRow] = u.mat[wave];
+  float(*head)[kMatRow] = head_all[wave];
   const int S = 1 + copies;
   const int half = lane >> 5, col = lane & 31;
-  const int kf = lane >> 1, h = lane & 1;
 
   // ---- letters of the window and its copies (4 for none)
   if (active) {
     const int64_t start = j * stride;
-    for (int s = 0; s < sp; ++s)
-      for (int p = lane; p < np; p += 64)
-        letters[s * np + p] = (s == 0 && p < N) ? (uint8_t)min((int)ref[start + p], 4) : (uint8_t)4;
+    for (int i = lane; i < sp * np / 16; i += 64)  // np is a multiple of 64
+      reinterpret_cast<uint4*>(letters)[i] = make_uint4(0x04040404u, 0x04040404u, 0x04040404u, 0x04040404u);
+    for (int p = lane; p < N; p += 64) letters[p] = (uint8_t)min((int)ref[start + p], 4);
+    // the reference letters that nearly every step reads (a copy with d more
+    // deletions than insertions reaches N + d)
+    const int n_own = (int)min<int64_t>(np + 64, G - start);
+    for (int p = lane; p < n_own; p += 64) own[p] = ref[start + p];
     __builtin_amdgcn_wave_barrier();
-    for (int c = 0; c < copies; ++c) {
-      uint8_t* out = letters + (size_t)(c + 1) * np;
-      int64_t pos = start;  // next reference letter
-      int n = 0;            // letters emitted
-      for (int t0 = 0; t0 < max_steps && n < N; t0 += 64) {
-        const int t = t0 + lane;
-        const Words4 d = philox4x32_10((uint32_t)j, (uint32_t)(j >> 32), (uint32_t)c, (uint32_t)t,
-                                       seed, 0u);
-        const bool live = t < max_steps;
-        // 0 insertion, 1 deletion, 2 substitution, 3 match
-        int kind = d.x < T1 ? 0 : d.x < 2u * T1 ? 1 : d.x < 3u * T1 ? 2 : 3;
-        const uint64_t consume = __ballot(live && kind != 0);
-        const int64_t p = pos + lanes_below(consume);
-        if (p >= G) kind = 0;
-        const bool emit = live && kind != 1;
-        const uint64_t em = __ballot(emit);
-        const int q = lanes_below(em);  // this step's output index in the group
-        if (emit && n + q < N) {
-          int L;
-          if (kind == 0) {
-            L = (int)(d.y & 3u);
-          } else {
-            const int R0 = ref[p];
-            L = (kind == 3 || R0 > 3) ? R0 : (R0 + 1 + (int)(d.z % 3u)) & 3;
-          }
-          out[n + q] = (uint8_t)min(L, 4);
+    // positions count from the window's start; a copy takes at most max_steps
+    const int end = (int)min<int64_t>(G - start, INT32_MAX);
+    // kDraw copies at a time: a step's draw, masks and letter are one dependent
+    // chain, and the LDS leaves two wavefronts per SIMD to hide it
+    for (int c = 0; c < copies; c += kDraw) {
+      int pos[kDraw], n[kDraw];  // next reference letter, letters emitted
+#pragma unroll
+      for (int u = 0; u < kDraw; ++u) {
+        pos[u] = 0;
+        n[u] = c + u < copies ? 0 : N;
+      }
+      for (int t0 = 0; t0 < max_steps; t0 += 64) {
+        int least = N;
+#pragma unroll
+        for (int u = 0; u < kDraw; ++u) least = min(least, n[u]);
+        if (least >= N) break;
+        Words4 d[kDraw];
+#pragma unroll
+        for (int u = 0; u < kDraw; ++u)
+          d[u] = philox4x32_10((uint32_t)j, (uint32_t)(j >> 32), (uint32_t)(c + u),
+                               (uint32_t)(t0 + lane), seed, 0u);
+        // The steps' kinds as wavefront masks, combined by scalar instructions:
+        // insertion below T1, deletion below 2 T1, substitution below 3 T1, else
+        // a match.
+        const uint64_t live = max_steps - t0 >= 64 ? ~0ull : (1ull << (max_steps - t0)) - 1;
+        uint64_t ins[kDraw], em[kDraw], sub[kDraw];
+        int p[kDraw], q[kDraw], L[kDraw];
+#pragma unroll
+        for (int u = 0; u < kDraw; ++u) {
+          const uint64_t ge1 = __ballot(d[u].x >= T1) & live, ge2 = __ballot(d[u].x >= 2u * T1);
+          sub[u] = ge2 & ~__ballot(d[u].x >= 3u * T1);
+          p[u] = lanes_below(ge1, pos[u]);  // reference position of the step
+          ins[u] = live & ~ge1;
+          if (pos[u] + 64 >= end) ins[u] |= __ballot(p[u] >= end) & live;  // past the reference
+          em[u] = ins[u] | (ge2 & live);
+          q[u] = lanes_below(em[u], n[u]);  // this step's output index
+          L[u] = own[min(p[u], np + 63)];
         }
-        n += min(__popcll(em), N - n);
-        pos += __popcll(__ballot(live && kind != 0));
+#pragma unroll
+        for (int u = 0; u < kDraw; ++u) {
+          if (pos[u] > np) {
+            if (p[u] >= np + 64 && p[u] < end) L[u] = ref[start + p[u]];
+          }
+          L[u] = min(L[u], 4);
+          if (sub[u]) {
+            const int other = (L[u] + 1 + (int)(d[u].z % 3u)) & 3;
+            L[u] = __builtin_amdgcn_inverse_ballot_w64(sub[u]) && L[u] < 4 ? other : L[u];
+          }
+          if (ins[u]) L[u] = __builtin_amdgcn_inverse_ballot_w64(ins[u]) ? (int)(d[u].y & 3u) : L[u];
+          const int n_em = __popcll(em[u]);
+          if (n[u] + n_em > N) em[u] &= __ballot(q[u] < N);
+          if (__builtin_amdgcn_inverse_ballot_w64(em[u])) letters[(c + u + 1) * np + q[u]] = (uint8_t)L[u];
+          n[u] = min(n[u] + n_em, N);
+          pos[u] += __popcll(live & ~ins[u]);
+        }
       }
     }
   }
 
-  float2 x0 = make_float2(0.f, 0.f), x1 = make_float2(0.f, 0.f);  // the window
-  float X = 0.f;
+  float X = 0.f;  // the window's squared norm
   float mine = 3.0e38f;  // lane c keeps copy c's fidelity
   const uint32_t onehot_tab = 0x40u << (8 * (col & 3));
   for (int s0 = 0; s0 < S; s0 += SMAX) {
@@ -263,6 +317,7 @@ __global__ __launch_bounds__(64 * kThrWaves) void window_thresholds_mfma_kernel(
         }
       }
     }
+    __syncthreads();  // the table parts are read: their LDS takes the products
     if (!active) continue;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
@@ -272,21 +327,16 @@ __global__ __launch_bounds__(64 * kThrWaves) void window_thresholds_mfma_kernel(
         for (int v = 0; v < 16; ++v)
           mat[8 * (v >> 2) + 4 * half + (v & 3)][cb * 32 + col] = 0.5f * acc[rb][cb][v];
       __builtin_amdgcn_wave_barrier();
-      for (int sl = 0; sl < 8; ++sl) {
-        const int sx = s0 + rb * 8 + sl;
-        if (rb * 8 + sl >= SP) break;
-        const float2 c0 = make_float2(mat[4 * sl + 2 * h][2 * kf], mat[4 * sl + 2 * h][2 * kf + 1]);
-        const float2 c1 = make_float2(mat[4 * sl + 2 * h + 1][2 * kf], mat[4 * sl + 2 * h + 1][2 * kf + 1]);
-        const float Y = wave_sum(c0.x * c0.x + c0.y * c0.y + c1.x * c1.x + c1.y * c1.y);
-        if (sx == 0) {
-          x0 = c0;
-          x1 = c1;
-          X = Y;
-          continue;
-        }
-        const float F = fidelity32(x0, x1, X, c0, c1, Y, N);
-        if (lane == sx - 1) mine = F;
+      if (s0 + rb == 0) {  // string 0 is the window
+        *reinterpret_cast<float4*>(&head[lane >> 4][4 * (lane & 15)]) =
+            *reinterpret_cast<const float4*>(&mat[lane >> 4][4 * (lane & 15)]);
+        __builtin_amdgcn_wave_barrier();
+        X = head_norm2(head, lane);
       }
+      const float F = strings_fidelity(mat, head, X, kDegenerateRel * N, lane);
+      const int own_s = lane + 1 - (s0 + rb * 8);  // this lane's copy as a string of the block
+      const float f = __shfl(F, 8 * (own_s & 7), 64);
+      if (own_s >= 0 && own_s < 8 && lane < copies) mine = f;
       __builtin_amdgcn_wave_barrier();  // before the next block overwrites mat
     }
   }
@@ -612,8 +662,9 @@ hipError_t launch_window_thresholds(const rm_index& idx, const uint8_t* ref, flo
   const int rb = min(5, (S + 7) / 8);
   const int sp = (S + 8 * rb - 1) / (8 * rb) * (8 * rb);
   const int np = (N + 63) / 64 * 64;
-  const size_t lds = (size_t)kThrWaves * sp * np;
-  if (copies <= 64 && lds <= 65536) {
+  const size_t letters = (size_t)kThrWaves * sp * np;
+  const size_t lds = letters + (size_t)kThrWaves * (np + 64);
+  if (copies <= 64 && letters <= 65536) {
     auto kern = rb <= 1 ? window_thresholds_mfma_kernel<1>
               : rb == 2 ? window_thresholds_mfma_kernel<2>
               : rb == 3 ? window_thresholds_mfma_kernel<3>

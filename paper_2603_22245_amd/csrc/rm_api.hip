@@ -238,8 +238,8 @@ static int encode_reference_impl(const uint8_t* d_ref, int64_t ref_len, const rm
                                                 idx.d_emb, idx.d_scale, idx.d_norm2, s));
   else
     st = hip_status(rm::launch_encode_reference_learned(d_ref, W, *p, idx.d_phase64,
-                                                        idx.d_phase32, idx.d_step32, d_delta,
-                                                        idx.d_emb, idx.d_scale, idx.d_norm2, s));
+                                                        d_delta, idx.d_emb, idx.d_scale,
+                                                        idx.d_norm2, s));
   if (st != RM_OK) return st;
   *out = idx;
   return RM_OK;

@@ -895,8 +895,47 @@ __global__ __launch_bounds__(256) void encode_reads_kernel(
 // s+N-8 enters at location N-9 (exp(i delta) times omega^(f_k (N-9)) is
 // added).  delta is row-major [tokens][32], FP32.
 
+// Sine and cosine in FP64: x = q pi/2 + r with pi/2 as the sum of two FP64
+// values, then the Taylor series on |r| <= pi/4, whose first left-out terms are
+// below 5e-17 (sine) and 3e-18 (cosine).
+__device__ __forceinline__ void sine_cosine64(double x, double* sn, double* cs) {
+  const double q = rint(x * 0.63661977236758134308);
+  double r = __builtin_fma(q, -1.5707963267948965580, x);
+  r = __builtin_fma(q, -6.1232339957367658861e-17, r);
+  const double r2 = r * r;
+  double s = -1.0 / 1307674368000.0, c = 1.0 / 20922789888000.0;
+  s = __builtin_fma(r2, s, 1.0 / 6227020800.0);
+  c = __builtin_fma(r2, c, -1.0 / 87178291200.0);
+  s = __builtin_fma(r2, s, -1.0 / 39916800.0);
+  c = __builtin_fma(r2, c, 1.0 / 479001600.0);
+  s = __builtin_fma(r2, s, 1.0 / 362880.0);
+  c = __builtin_fma(r2, c, -1.0 / 3628800.0);
+  s = __builtin_fma(r2, s, -1.0 / 5040.0);
+  c = __builtin_fma(r2, c, 1.0 / 40320.0);
+  s = __builtin_fma(r2, s, 1.0 / 120.0);
+  c = __builtin_fma(r2, c, -1.0 / 720.0);
+  s = __builtin_fma(r2, s, -1.0 / 6.0);
+  c = __builtin_fma(r2, c, 1.0 / 24.0);
+  s = __builtin_fma(r2 * r, s, r);
+  c = __builtin_fma(r2, c, -0.5);
+  c = __builtin_fma(r2, c, 1.0);
+  const int n = (int)q;
+  const double u = (n & 1) ? c : s, v = (n & 1) ? s : c;
+  *sn = (n & 2) ? -u : u;
+  *cs = ((n + 1) & 2) ? -v : v;
+}
+
+// The value of the other lane of the pair (lane ^ 1).
+__device__ __forceinline__ double partner64(double v) {
+  int2 w = __builtin_bit_cast(int2, v);
+  w.x = __builtin_amdgcn_mov_dpp(w.x, 0xB1, 0xf, 0xf, true);
+  w.y = __builtin_amdgcn_mov_dpp(w.y, 0xB1, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, w);
+}
+
 // FP64 direct sum over the tokens p = 0..N-9 of a string whose token offsets
-// are rows drow[p] (lane's two components).
+// are rows drow[p] (lane's two components).  A factor's two lanes need the same
+// terms: lane h forms those of every other token and hands them to its partner.
 __device__ __forceinline__ void direct_sum_learned(const uint8_t* __restrict__ str, int N,
                                                    const float* __restrict__ drow,
                                                    const double2* __restrict__ phase64, int lane,
@@ -910,47 +949,94 @@ __device__ __forceinline__ void direct_sum_learned(const uint8_t* __restrict__ s
     int mine = (pb + lane < T) ? (int)str[pb + lane + 4] : 255;
     int cnt = min(64, T - pb);
     for (int i0 = 0; i0 < cnt; i0 += 8) {
-      double2 e[8];
-      float d[8];
+      double2 e[4];
+      float d[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int p = min(pb + i0 + u, T - 1);
+      for (int u = 0; u < 4; ++u) {
+        const int p = min(pb + i0 + 2 * u + h, T - 1);
         e[u] = phase64[(int64_t)p * kM + k];
         d[u] = drow[(int64_t)p * 32 + k];
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        int L = __builtin_amdgcn_readlane(mine, i0 + u);
+      for (int u = 0; u < 4; ++u) {
+        const int even = __builtin_amdgcn_readlane(mine, i0 + 2 * u);
+        const int odd = __builtin_amdgcn_readlane(mine, i0 + 2 * u + 1);
         double sn, cs;
-        sincos((double)d[u], &sn, &cs);
+        sine_cosine64((double)d[u], &sn, &cs);
         const double er = e[u].x * cs - e[u].y * sn, ei = e[u].x * sn + e[u].y * cs;
-        a0.x += (L == L0) ? er : 0.0;
-        a0.y += (L == L0) ? ei : 0.0;
-        a1.x += (L == L1) ? er : 0.0;
-        a1.y += (L == L1) ? ei : 0.0;
+        const double pr = partner64(er), pi = partner64(ei);
+        const int own = h ? odd : even, other = h ? even : odd;
+        a0.x += (own == L0) ? er : 0.0;
+        a0.y += (own == L0) ? ei : 0.0;
+        a1.x += (own == L1) ? er : 0.0;
+        a1.y += (own == L1) ? ei : 0.0;
+        a0.x += (other == L0) ? pr : 0.0;
+        a0.y += (other == L0) ? pi : 0.0;
+        a1.x += (other == L1) ? pr : 0.0;
+        a1.y += (other == L1) ? pi : 0.0;
       }
     }
   }
 }
 
-constexpr int kChunk = 32;  // slides whose token terms are staged in LDS at once
+// The learned rolling encoder.  Within a chunk of kChunk slides the state is
+// kept in the frame of the chunk's first window: tokens leave and enter with
+// their phase there, theta_k times their distance from that window's start
+// plus their offset, and only an emitted window is turned into its own frame
+// (and the state once per chunk).  The terms of a chunk's 2 kChunk tokens are
+// formed first, one (token, factor) per lane, and wait in LDS; a slide then
+// adds the entering and takes away the leaving token with multipliers that the
+// pair of middle letters selects, eight multiply-adds.
+//
+// Bound by VALU issue: about 75 instructions a stride-1 window, of which the
+// two tokens' sines and cosines take 30.  They are the hardware's, of an angle
+// in turns: 1.8 against 1.9 ms with a polynomial, at the same error.  10^7
+// windows of 150 letters in FP16: 1.8 ms; 4.57 ms with a rotation, two complex
+// products and selects per slide and library sines in the re-anchors, at four
+// times the error (a squared norm is off by 1.2e-7 of itself, against 9.4e-7,
+// for the terms are exact in their own chunk and the state turns once in 16
+// slides).
+constexpr int kChunk = 16;
+constexpr int kLearnedBlocks = 4;  // resident blocks per CU
 
 template <int PREC>
-__global__ __launch_bounds__(256) void encode_reference_learned_kernel(
+__global__ __launch_bounds__(256, kLearnedBlocks) void encode_reference_learned_kernel(
     const uint8_t* __restrict__ ref, int64_t W, int N, int stride, int64_t seg_len, int64_t n_seg,
-    const double2* __restrict__ phase64, const float2* __restrict__ phase32,
-    const float4* __restrict__ step32, const float* __restrict__ delta, void* __restrict__ emb,
-    float* __restrict__ scale, float* __restrict__ norm2) {
-  // per wavefront: exp(i delta) of the outgoing (row 0..31) and incoming
-  // (rows 32..63) tokens of the current chunk of slides
-  __shared__ float2 u_stage[4][2 * kChunk][32];
+    int schedule, const double2* __restrict__ phase64, const float* __restrict__ delta,
+    void* __restrict__ emb, float* __restrict__ scale, float* __restrict__ norm2) {
+  __shared__ float2 terms[4][2 * kChunk][32];   // rows 0..: leaving, kChunk..: entering
+  __shared__ float2 turn[kChunk + 1][32];       // omega^(-f i)
+  __shared__ float4 pair_mul[25][2];            // [5 out + in][h]: -m(out), m(in)
+  const auto factor = [&](int kk) {
+    return schedule == RM_SCHED_FINETUNED ? 2.0 * kk / (kM - 1) + 1.0 : kk + 1.0;
+  };
+  for (int v = threadIdx.x; v < (kChunk + 1) * 32; v += 256) {
+    const double t = factor(v & 31) * (v >> 5) / N;
+    double sn, cs;
+    sine_cosine64((t - rint(t)) * 6.2831853071795862320, &sn, &cs);
+    turn[v >> 5][v & 31] = make_float2((float)cs, -(float)sn);
+  }
+  if (threadIdx.x < 50) {
+    const int e = threadIdx.x >> 1, hh = threadIdx.x & 1;
+    const LetterMul out = letter_mul_entry(hh, e / 5), in = letter_mul_entry(hh, e % 5);
+    pair_mul[e][hh] = make_float4(-out.m0, -out.m1, in.m0, in.m1);
+  }
+  __syncthreads();
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t seg = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
   if (seg >= n_seg) return;
   const int k = lane >> 1, h = lane & 1;
-  const int L0 = 2 * h, L1 = 2 * h + 1;
   const int64_t j0 = seg * seg_len;
   const int64_t j1 = min(W, j0 + seg_len);
+  // The phase of position p of the chunk for the factor of this lane's terms, in
+  // units of 2^-32 turns (modulo one turn): p = 0 and 1 leaving, N-8 and N-7
+  // entering, and the step of two positions.
+  const double fn = factor(lane & 31) / N;
+  const auto fixed_turns = [&](int p) {
+    return (uint32_t)(int64_t)rint(4294967296.0 * (fn * p - rint(fn * p)));
+  };
+  const uint32_t leave0 = fixed_turns(lane >> 5), enter0 = fixed_turns(N - 8 + (lane >> 5));
+  const uint32_t step2 = fixed_turns(2);
 
   double2 a0, a1;
   const int64_t s0 = j0 * stride;
@@ -960,46 +1046,55 @@ __global__ __launch_bounds__(256) void encode_reference_learned_kernel(
   SideBuf side{j0, 0, 0.f, 0.f, PREC == RM_FP8_E4M3 ? scale + W : nullptr, 0.f};
   emit_window<PREC>(j0, lane, N, c0, c1, emb, side, scale, norm2);
 
-  const float4 st = step32[k];
-  const float2 rot = make_float2(st.x, st.y);    // omega^-f
-  const float2 inc = phase32[(int64_t)(N - 9) * kM + k];  // omega^(f (N-9))
-  float2(*stage)[32] = u_stage[wave];
-
+  float2(*term)[32] = terms[wave];
   const int64_t n_slides = (j1 - 1 - j0) * stride;
   int64_t j = j0;
   int until_emit = stride;
   for (int64_t tb = 0; tb < n_slides; tb += kChunk) {
     const int cnt = (int)min<int64_t>(kChunk, n_slides - tb);
-    // stage exp(i delta) of tokens s0+tb+i (out) and s0+tb+i+N-8 (in), i < cnt
-#pragma unroll 4
-    for (int q = 0; q < 2 * kChunk * 32 / 64; ++q) {
-      const int v = q * 64 + lane;
-      const int row = v >> 5, kk = v & 31;
-      const int i = row & (kChunk - 1);
-      if (i < cnt) {
-        const int64_t tok = s0 + tb + i + (row >= kChunk ? N - 8 : 0);
-        float sn, cs;
-        __sincosf(delta[tok * 32 + kk], &sn, &cs);  // hardware sin/cos: ~1e-6 for offsets of a few radians
-        stage[row][kk] = make_float2(cs, sn);
-      }
+    // tokens s0+tb+i (leaving) and s0+tb+i+N-8 (entering), i < cnt
+    float d[kChunk];
+#pragma unroll
+    for (int q = 0; q < kChunk; ++q) {
+      const int row = 2 * q + (lane >> 5), i = min(row & (kChunk - 1), cnt - 1);
+      d[q] = delta[(s0 + tb + i + (row >= kChunk ? N - 8 : 0)) * 32 + (lane & 31)];
+    }
+    // their letters' pair: leaving ref[s0+t+4], entering ref[s0+t+N-4]
+    int pair = 24;
+    if (lane < cnt)
+      pair = 5 * min((int)ref[s0 + tb + lane + 4], 4) + min((int)ref[s0 + tb + lane + N - 4], 4);
+#pragma unroll
+    for (int q = 0; q < kChunk; ++q) {
+      const int row = 2 * q + (lane >> 5);
+      float sn, cs;
+      const uint32_t at = (q < kChunk / 2 ? leave0 : enter0) + (uint32_t)(q % (kChunk / 2)) * step2;
+      // in turns; the offset's whole ones are taken off before it is rounded
+      const float whole = rintf(d[q] * 0.15915494f);
+      const float z = fmaf(d[q], 0.15915494f, -whole) +
+                      fmaf((float)(int)at, 0x1p-32f, d[q] * 6.4206e-9f);
+      sn = __builtin_amdgcn_sinf(z);
+      cs = __builtin_amdgcn_cosf(z);
+      term[row][lane & 31] = make_float2(cs, sn);
     }
     __builtin_amdgcn_wave_barrier();
-    // letters: outgoing token middle ref[s0+t+4], incoming ref[s0+t+N-4]
-    const int64_t t = tb + (lane & (kChunk - 1));
-    const bool in_half = lane >= kChunk;
-    int mine = 255;
-    if ((lane & (kChunk - 1)) < cnt) mine = (int)ref[s0 + t + (in_half ? N - 4 : 4)];
     for (int i = 0; i < cnt; ++i) {
-      const int o = __builtin_amdgcn_readlane(mine, i);
-      const int n = __builtin_amdgcn_readlane(mine, i + kChunk);
-      slide(c0, c1, rot, o, n, h, cmul(stage[i][k], rot), cmul(stage[kChunk + i][k], inc));
+      const float4 m = pair_mul[__builtin_amdgcn_readlane(pair, i)][h];
+      const float2 out = term[i][k], in = term[kChunk + i][k];
+      c0.x = fmaf(m.z, in.x, fmaf(m.x, out.x, c0.x));
+      c0.y = fmaf(m.z, in.y, fmaf(m.x, out.y, c0.y));
+      c1.x = fmaf(m.w, in.x, fmaf(m.y, out.x, c1.x));
+      c1.y = fmaf(m.w, in.y, fmaf(m.y, out.y, c1.y));
       if (--until_emit == 0) {
         until_emit = stride;
         ++j;
-        emit_window<PREC>(j, lane, N, c0, c1, emb, side, scale, norm2);
+        const float2 t = turn[i + 1][k];
+        emit_window<PREC>(j, lane, N, cmul(c0, t), cmul(c1, t), emb, side, scale, norm2);
       }
     }
-    __builtin_amdgcn_wave_barrier();  // the stage is rewritten by the next chunk
+    const float2 t = turn[cnt][k];
+    c0 = cmul(c0, t);
+    c1 = cmul(c1, t);
+    __builtin_amdgcn_wave_barrier();  // the terms are rewritten by the next chunk
   }
   side_finish(side, lane, norm2, scale);
 }
@@ -1276,34 +1371,41 @@ hipError_t launch_encode_reads(const rm_params& p, const float* phase32, const u
 namespace rm {
 
 hipError_t launch_encode_reference_learned(const uint8_t* ref, int64_t W, const rm_params& p,
-                                           const double* phase64, const float* phase32,
-                                           const float* step32, const float* delta, void* emb,
+                                           const double* phase64, const float* delta, void* emb,
                                            float* scale, float* norm2, hipStream_t s) {
+  // Segments: the caller's value, or as few rounds of resident wavefronts as
+  // keep a segment within 2048 starts, each round full (a last round that is
+  // partly empty costs as much as a full one: 10^7 starts 1.98
+  // against 1.82 ms), and short ones rather than an idle chip: 50,000 starts,
+  // offsets included, 70 us in segments of 32 and 134 us in segments of 256
+  const int waves = 4;
   int64_t seg = p.reanchor;
   if (seg <= 0) {
-    seg = (W + 8191) / 8192;
-    if (seg < 256) seg = 256;
-    if (seg > 4096) seg = 4096;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus < 1)
+      cus = 256;
+    const int64_t resident = (int64_t)kLearnedBlocks * cus * waves;
+    const int64_t rounds = std::max<int64_t>(1, (W + 2048 * resident - 1) / (2048 * resident));
+    seg = std::max<int64_t>(32, (W + rounds * resident - 1) / (rounds * resident));
   }
   int64_t n_seg = (W + seg - 1) / seg;
-  const int waves = 4;
   int64_t blocks = (n_seg + waves - 1) / waves;
   auto* ph = reinterpret_cast<const double2*>(phase64);
-  auto* p32 = reinterpret_cast<const float2*>(phase32);
-  auto* st = reinterpret_cast<const float4*>(step32);
   const dim3 grid((unsigned)blocks), block(64 * waves);
   switch (p.precision) {
     case RM_FP32:
       hipLaunchKernelGGL(encode_reference_learned_kernel<RM_FP32>, grid, block, 0, s, ref, W,
-                         p.window_len, p.stride, seg, n_seg, ph, p32, st, delta, emb, scale, norm2);
+                         p.window_len, p.stride, seg, n_seg, p.schedule, ph, delta, emb, scale, norm2);
       break;
     case RM_FP16:
       hipLaunchKernelGGL(encode_reference_learned_kernel<RM_FP16>, grid, block, 0, s, ref, W,
-                         p.window_len, p.stride, seg, n_seg, ph, p32, st, delta, emb, scale, norm2);
+                         p.window_len, p.stride, seg, n_seg, p.schedule, ph, delta, emb, scale, norm2);
       break;
     default:
       hipLaunchKernelGGL(encode_reference_learned_kernel<RM_FP8_E4M3>, grid, block, 0, s, ref, W,
-                         p.window_len, p.stride, seg, n_seg, ph, p32, st, delta, emb, scale, norm2);
+                         p.window_len, p.stride, seg, n_seg, p.schedule, ph, delta, emb, scale, norm2);
       break;
   }
   return hipGetLastError();

@@ -43,16 +43,52 @@ __device__ __forceinline__ unsigned short bf16_bits(float x) {
 
 __device__ __forceinline__ bf16x8 as_bf16(u16x8 v) { return __builtin_bit_cast(bf16x8, v); }
 
-__global__ __launch_bounds__(64 * kWavesPerBlock) void mlp_infer_kernel(
+// The letters t..t+8 of a lane's token.
+struct Letters {
+  uint32_t first, last;  // w[t..t+3], w[t+5..t+8], one byte each
+  int mid;
+};
+
+__device__ __forceinline__ Letters load_letters(const uint8_t* __restrict__ seq, int64_t t,
+                                                int64_t n_tok) {
+  Letters l{0x04040404u, 0x04040404u, 4};
+  if (t < n_tok) {
+    __builtin_memcpy(&l.first, seq + t, 4);
+    __builtin_memcpy(&l.last, seq + t + 5, 4);
+    l.mid = seq[t + 4];
+  }
+  return l;
+}
+
+// One letter's four inputs, 1.0 at the letter's and none beyond the fourth.
+__device__ __forceinline__ uint2 onehot(uint32_t letter) {
+  const uint64_t v = letter < 4 ? (uint64_t)0x3F80 << (16 * letter) : 0;
+  return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+}
+
+// Bound by its stores (128 bytes a token) and VALU issue.  Lane l holds 16-byte
+// pieces of a token's row; they go through LDS, so that a store instruction
+// writes 1 KB in a row and not halves of 32 lines, and the next tile's letters
+// are loaded (three loads) before this tile's products.  10^7 letters: 400 us,
+// 3.2 TB/s; 700 us with 16-byte stores 32
+// bytes apart, nine byte loads in the chain, and the rounding done in integers.
+__global__ __launch_bounds__(64 * kWavesPerBlock, 2) void mlp_infer_kernel(
     const float* __restrict__ params, const uint8_t* __restrict__ seq, int64_t n_tok,
     float* __restrict__ delta) {
-  __shared__ float sb1[kHid], sb2[kOut];
-  for (int i = threadIdx.x; i < kHid; i += blockDim.x) sb1[i] = params[kB1 + i];
-  for (int i = threadIdx.x; i < kOut; i += blockDim.x) sb2[i] = params[kB2 + i];
+  __shared__ float sb2[kOut + 32];  // the last row, of other letters, is 0
+  __shared__ float rows[kWavesPerBlock][32][36];  // 36: 16 lanes' 16 bytes on 64 banks
+  for (int i = threadIdx.x; i < kOut + 32; i += blockDim.x) sb2[i] = i < kOut ? params[kB2 + i] : 0.f;
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 5, col = lane & 31;
 
+  // the biases of the lane's hidden rows, the first products' addend
+  floatx16 b1[2];
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      b1[mt][v] = params[kB1 + 32 * mt + 8 * (v >> 2) + 4 * g + (v & 3)];
   // weight fragments (A operands), rounded once per wavefront
   bf16x8 w1f[2][2];
 #pragma unroll
@@ -79,37 +115,20 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void mlp_infer_kernel(
     }
 
   const int64_t n_tiles = (n_tok + 31) / 32;
-  for (int64_t tile = (int64_t)blockIdx.x * kWavesPerBlock + wave; tile < n_tiles;
-       tile += (int64_t)gridDim.x * kWavesPerBlock) {
-    const int64_t t = tile * 32 + col;  // this lane's token
-    const bool valid = t < n_tok;
-    int let[9];
-#pragma unroll
-    for (int q = 0; q < 9; ++q) let[q] = valid ? (int)seq[t + q] : 4;
+  const int64_t step = (int64_t)gridDim.x * kWavesPerBlock;
+  int64_t tile = (int64_t)blockIdx.x * kWavesPerBlock + wave;
+  Letters next = load_letters(seq, tile * 32 + col, n_tok);
+  for (; tile < n_tiles; tile += step) {
+    const Letters let = next;  // of token 32 tile + col
+    next = load_letters(seq, (tile + step) * 32 + col, n_tok);
 
-    // layer 1, accumulators start at b1 of the lane's hidden rows
-    floatx16 acc1[2];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 b = *reinterpret_cast<const float4*>(&sb1[32 * mt + 8 * q + 4 * g]);
-        acc1[mt][4 * q] = b.x;
-        acc1[mt][4 * q + 1] = b.y;
-        acc1[mt][4 * q + 2] = b.z;
-        acc1[mt][4 * q + 3] = b.w;
-      }
+    // layer 1.  Inputs 16ks + 8g + j: flank 4ks + 2g + j/4, letter j%4
+    floatx16 acc1[2] = {b1[0], b1[1]};
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      // inputs 16ks + 8g + j: flank 4ks + 2g + j/4, letter j%4
-      u16x8 x;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int fi = 4 * ks + 2 * g + (j >> 2);
-        const int pos = fi < 4 ? fi : fi + 1;
-        x[j] = let[pos] == (j & 3) ? (unsigned short)0x3F80 : (unsigned short)0;
-      }
-      const bf16x8 xb = as_bf16(x);
+      const uint32_t w = (ks ? let.last : let.first) >> (16 * g);
+      const uint2 lo = onehot(w & 255), hi = onehot(w >> 8 & 255);
+      const bf16x8 xb = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
         acc1[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1f[mt][ks], xb, acc1[mt], 0, 0, 0);
@@ -119,13 +138,11 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void mlp_infer_kernel(
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       const int mt = ks >> 1, half = ks & 1;
-      u16x8 v;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = bf16_bits(fmaxf(acc1[mt][8 * half + j], 0.f));
-      hf[ks] = as_bf16(v);
+      for (int j = 0; j < 8; ++j) hf[ks][j] = (__bf16)__builtin_amdgcn_fmed3f(acc1[mt][8 * half + j], 0.f, INFINITY);
     }
     // layer 2, one letter tile at a time; keep the middle letter's
-    const int mid = let[4];
+    const int mid = let.mid;
     floatx16 res;
 #pragma unroll
     for (int v = 0; v < 16; ++v) res[v] = 0.f;
@@ -140,19 +157,22 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void mlp_infer_kernel(
 #pragma unroll
       for (int v = 0; v < 16; ++v) res[v] = mid == mo ? acc2[v] : res[v];
     }
-    if (valid) {
-      float* dst = delta + t * 32 + 4 * g;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (mid < 4) {
-          const float4 b = *reinterpret_cast<const float4*>(&sb2[32 * mid + 8 * q + 4 * g]);
-          o = make_float4(res[4 * q] + b.x, res[4 * q + 1] + b.y, res[4 * q + 2] + b.z,
-                          res[4 * q + 3] + b.w);
-        }
-        *reinterpret_cast<float4*>(dst + 8 * q) = o;
-      }
+    for (int q = 0; q < 4; ++q) {
+      const float4 b = *reinterpret_cast<const float4*>(&sb2[32 * min(mid, 4) + 8 * q + 4 * g]);
+      *reinterpret_cast<float4*>(&rows[wave][col][8 * q + 4 * g]) = make_float4(
+          res[4 * q] + b.x, res[4 * q + 1] + b.y, res[4 * q + 2] + b.z, res[4 * q + 3] + b.w);
     }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = 8 * q + (lane >> 3);
+      const int64_t t = tile * 32 + r;
+      if (t < n_tok)
+        *reinterpret_cast<float4*>(delta + t * 32 + 4 * (lane & 7)) =
+            *reinterpret_cast<const float4*>(&rows[wave][r][4 * (lane & 7)]);
+    }
+    __builtin_amdgcn_wave_barrier();  // the rows are rewritten by the next tile
   }
 }
 
@@ -163,7 +183,7 @@ hipError_t launch_mlp_infer(const float* params, const uint8_t* seq, int64_t n_l
   const int64_t n_tok = n_letters - 8;
   const int64_t tiles = (n_tok + 31) / 32;
   int64_t blocks = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
-  if (blocks > 1024) blocks = 1024;  // grid-stride beyond: weights are loaded once per wavefront
+  if (blocks > 512) blocks = 512;  // all resident: a wavefront loads the weights once
   hipLaunchKernelGGL(mlp_infer_kernel, dim3((unsigned)blocks), dim3(64 * kWavesPerBlock), 0, s,
                      params, seq, n_tok, delta);
   return hipGetLastError();

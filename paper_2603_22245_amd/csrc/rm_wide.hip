@@ -14,12 +14,21 @@
 // (three in flight while one is computed), eight wavefronts of 64 x 128
 // outputs on 32x32x16 FP16 (32x32x64 FP8) MFMAs.  The block tile is as large
 // as the 160 KB of LDS allows, since its reuse sets the bytes copied per
-// flop.  Per tile the epilogue writes F = Re^2 + Im^2 of every (read, window)
-// to LDS and each wavefront compares 16 reads' scores with their current
-// k-th best; the (rare) hits are inserted into the read's sorted list held in
-// LDS.  A block walks the window tiles of one chunk and writes each read's
-// list; a merge kernel keeps the k best over the chunks.
+// flop.  The copies run on from tile to tile.  The epilogue forms F = Re^2 +
+// Im^2 in registers and hands the (rare) scores that reach a read's k-th best
+// to the read's sorted list held in LDS.  A block walks the window tiles of one
+// chunk and writes each read's list; a merge kernel keeps the k best over the
+// chunks.
+//
+// Bound by the matrix cores.  20,000 reads x 625,000 windows in FP8: 45.9 ms,
+// 2.2 PFLOP/s (38.4 ms of products alone, 3.8 of comparisons, 3.7 of ranking);
+// 58.0 ms when a stage's operands were read and then multiplied, every score
+// went through LDS, the next tile's copies waited for that, and every chunk's
+// lists started empty.  128 x 128 outputs of four wavefronts, with a third less
+// to read from LDS, were slower (one wavefront per SIMD hides no epilogue).
 #include "rm_tokens.h"
+
+#include <type_traits>
 
 namespace rm {
 
@@ -36,6 +45,10 @@ constexpr int kTM = 64 * kWM;       // A rows per block tile (kTM / 2 reads)
 constexpr int kTN = 32 * kGN * kWN; // windows per block tile
 constexpr int kLine = 64;   // bytes of every row per K stage (32 FP16 or 64 FP8 elements)
 constexpr int kListMax = RM_WIDE_MAX_KFETCH;
+constexpr int kHitMax = 15;  // of a read, wavefront and round of the epilogue
+static_assert(kListMax <= 32 && kWN * kHitMax <= 32,
+              "a list and the hits of a round are one wavefront's keys");
+static_assert(kTM / 2 == 128 && kWaves == 8 && kWN == 2, "two reads' counts a lane, 16 reads a wavefront");
 constexpr int kGroupTiles = 8;   // read tiles per group of 32 blocks on one XCD
 constexpr int kGroupChunks = 4;  // window chunks per group
 
@@ -254,12 +267,12 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 }
 
 // Asynchronous copy of 16 bytes per lane from global memory straight into LDS
-// (gfx950 global_load_lds_dwordx4): lane l writes LDS bytes [lds + 16 l,
-// lds + 16 l + 16).  No output register; completion is awaited with
-// wait_vm<N>(), which counts this wavefront's vector-memory operations in
-// issue order.  The LDS base goes in through an m0 operand.
-__device__ __forceinline__ void dma16w(const void* src, uint32_t lds) {
-  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(lds) : "memory");
+// (gfx950 global_load_lds_dwordx4): lane l copies the 16 bytes at base + off to
+// LDS bytes [lds + 16 l, lds + 16 l + 16).  No output register; completion is
+// awaited with wait_vm<N>(), which counts this wavefront's vector-memory
+// operations in issue order.  The LDS base goes in through an m0 operand.
+__device__ __forceinline__ void dma16w(const uint8_t* base, uint32_t off, uint32_t lds) {
+  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(lds) : "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_vm() {
@@ -277,6 +290,9 @@ constexpr int kRing = 4;                             // stages in LDS (three in 
 constexpr int kDmaPerWave = (kTM + kTN) * kChunks / (64 * kWaves);  // copies per lane per stage
 static_assert(kDmaPerWave * 64 * kWaves == (kTM + kTN) * kChunks, "stage splits into whole copies");
 static_assert((kRing - 2) * kDmaPerWave <= 63, "vmcnt range");
+constexpr int kDmaA = kTM * kChunks / (64 * kWaves);  // of them of A rows
+static_assert(kDmaA * 64 * kWaves == kTM * kChunks, "a copy is of one operand");
+static_assert(kLine == 64 && kGN == 4 && kRing == 4, "two 16-byte chunks a lane and row block, two halves");
 
 __device__ __forceinline__ int swz(int row) { return (row / kRowsPerBankRow) % kChunks; }
 __device__ __forceinline__ uint32_t chunk_pos(int row, int c) {
@@ -292,6 +308,13 @@ __device__ __forceinline__ uint32_t chunk_pos(int row, int c) {
 // blocks at about the same time.  Writes the k_fetch best keys of each of the
 // tile's reads over the chunk to part[read][chunk][0..k_fetch) (0 = empty).
 //
+// Groups go through all read tiles before the next four chunks.  A block starts
+// from the largest k-th best of its reads' chunks that are done: what does not
+// beat it is not among the read's k best.  (Any value it finds there, a chunk's
+// k-th best or the 0 that the entries are cleared to, is a lower bound, so the
+// result does not depend on which chunks are done.)  A chunk of 31,000 windows
+// ranks about 250 keys a read from an empty list and 30 from another's k-th best.
+//
 // FP16: 32x32x16 MFMAs, F = Re^2 + Im^2.  FP8: 32x32x64 MFMAs on the e4m3
 // codes, F = (Re^2 + Im^2) (s_r s_j)^2 with the read's and the window's
 // scales.
@@ -299,13 +322,17 @@ template <int PREC>
 __global__ __launch_bounds__(kThreads, 1) void score_wide_kernel(
     const uint8_t* __restrict__ A, const float* __restrict__ a_scale, int32_t n_reads,
     const uint8_t* __restrict__ B, const float* __restrict__ b_scale, int64_t W,
-    int n_rt, int64_t n_tiles, int64_t chunk_tiles, int n_chunks, int n_quads, int k_fetch,
+    int n_rt, int64_t n_tiles, int64_t chunk_tiles, int n_chunks, int k_fetch,
     uint64_t* __restrict__ part) {
-  // the stage ring, reused by the epilogue as the F buffer [kTM / 2 reads][kTN]
+  // the stage ring; between tiles its last slot takes the tile's hits
   __shared__ __attribute__((aligned(1024))) uint8_t ring[kRing][kStageBytes];
   __shared__ uint64_t lists[kTM / 2][kListMax];
-  static_assert(sizeof(float) * (kTM / 2) * kTN <= sizeof(ring), "F buffer fits in the ring");
-  float* Fbuf = reinterpret_cast<float*>(&ring[0][0]);
+  struct Hits {
+    uint64_t key[kTM / 2][kWN][kHitMax];
+    uint32_t count[kTM / 2][kWN];
+  };
+  static_assert(sizeof(Hits) <= kStageBytes, "the hits fit in a ring slot");
+  Hits& hits = *reinterpret_cast<Hits*>(&ring[kRing - 1][0]);
   constexpr bool kFp8 = PREC == RM_FP8_E4M3;
   constexpr int64_t kRowBytes = (int64_t)kWR * (kFp8 ? 1 : 2);
   constexpr int kStages = (int)(kRowBytes / kLine);
@@ -315,8 +342,9 @@ __global__ __launch_bounds__(kThreads, 1) void score_wide_kernel(
   const int wr = wave / kWN, wc = wave % kWN;  // this wavefront's 64 rows x 32 kGN windows
   const int xcd = blockIdx.x % 8, i_x = blockIdx.x / 8;
   const int group = (i_x / 32) * 8 + xcd, j_g = i_x % 32;
-  const int rt = (group / n_quads) * kGroupTiles + j_g / kGroupChunks;
-  const int chunk = (group % n_quads) * kGroupChunks + j_g % kGroupChunks;
+  const int n_rt_groups = (n_rt + kGroupTiles - 1) / kGroupTiles;
+  const int rt = (group % n_rt_groups) * kGroupTiles + j_g / kGroupChunks;
+  const int chunk = (group / n_rt_groups) * kGroupChunks + j_g % kGroupChunks;
   if (rt >= n_rt || chunk >= n_chunks) return;  // the whole block, before any barrier
   const int64_t row0 = (int64_t)rt * kTM;  // first A row (= 2 x first read)
   const int64_t M = 2 * (int64_t)n_reads;
@@ -324,59 +352,74 @@ __global__ __launch_bounds__(kThreads, 1) void score_wide_kernel(
   const int64_t t1 = min(n_tiles, t0 + chunk_tiles);
   const uint32_t ring_lds = lds_addr(&ring[0][0]);
 
-  for (int i = tid; i < (kTM / 2) * kListMax; i += kThreads) (&lists[0][0])[i] = 0;
-
-  // FP8: squared scales of this lane's reads (output rows 2q, 2q+1 of a 32-row
-  // block hold read q; see the epilogue) -- and, per tile, of its windows
-  float sr2[2][8];
-#pragma unroll
-  for (int f = 0; f < 2; ++f)
-#pragma unroll
-    for (int vv = 0; vv < 8; ++vv) {
-      sr2[f][vv] = 1.f;
-      if constexpr (kFp8) {
-        const int v = 2 * vv;
-        const int row = 64 * wr + 32 * f + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        const int64_t r = row0 / 2 + (row >> 1);
-        const float sc = r < n_reads ? a_scale[r] : 0.f;
-        sr2[f][vv] = sc * sc;
-      }
+  // A list starts full of the read's largest k-th best elsewhere (0: none yet),
+  // which the end takes out again.  Nothing beats those of reads past the last.
+  uint64_t seed = ~(uint64_t)0;
+  if (tid < kTM / 2) {
+    const int64_t r = row0 / 2 + tid;
+    if (r < n_reads) {
+      seed = 0;
+      for (int c = 0; c < n_chunks; ++c)
+        seed = max(seed, __hip_atomic_load(&part[(r * n_chunks + c) * k_fetch + k_fetch - 1],
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     }
+    for (int i = 0; i < k_fetch; ++i) lists[tid][i] = seed;
+  }
 
   // This lane's 16-byte pieces of a stage: piece p = 64 (wave + kWaves i) +
   // lane lands at LDS position p (row p / kChunks, position p % kChunks) and
-  // holds chunk (p % kChunks) ^ swz(row) of that row.  Rows past the last read or
-  // window re-read the last one (always in bounds); their scores are never
-  // used.
-  int64_t src_off[kDmaPerWave];  // byte offset of the piece's row and chunk, K stage 0
-  bool is_b[kDmaPerWave];
+  // holds chunk (p % kChunks) ^ swz(row) of that row; the first half of the i
+  // are A rows.  Rows past the last read or window re-read the last one (always
+  // in bounds); their scores are never used.
+  const uint8_t* a_base = A + row0 * kRowBytes;
+  uint32_t piece_row[kDmaPerWave], piece_col[kDmaPerWave];
 #pragma unroll
   for (int i = 0; i < kDmaPerWave; ++i) {
     const int p = 64 * (wave + kWaves * i) + lane;
     const int row = p / kChunks;
-    const int c = (p % kChunks) ^ swz(row);
-    is_b[i] = row >= kTM;
-    src_off[i] = (is_b[i] ? (int64_t)(row - kTM) : min(row0 + row, M - 1)) * kRowBytes + c * 16;
+    piece_col[i] = 16 * ((p % kChunks) ^ swz(row));
+    piece_row[i] = i < kDmaA ? (uint32_t)(min(row0 + row, M - 1) - row0) : row - kTM;
   }
   // Stage st of a tile holds K line st, or line kStages - 1 - st on every
   // other tile of the chunk: a tile then starts on the read rows' lines the
   // previous one ended on, which the XCD's L2 still holds.
-  auto issue = [&](int64_t tile, int st) {
-    const uint32_t base = ring_lds + (uint32_t)(st % kRing) * kStageBytes;
-    const int64_t kl = (int64_t)(((tile - t0) & 1) ? kStages - 1 - st : st) * kLine;
+  uint32_t off_a[kDmaA];
 #pragma unroll
-    for (int i = 0; i < kDmaPerWave; ++i) {
-      const uint8_t* src;
-      if (is_b[i]) {
-        const int64_t g = min(tile * kTN + src_off[i] / kRowBytes, W - 1);
-        src = B + g * kRowBytes + (src_off[i] % kRowBytes) + kl;
-      } else {
-        src = A + src_off[i] + kl;
-      }
-      dma16w(src, __builtin_amdgcn_readfirstlane(base + 1024 * (wave + kWaves * i)));
+  for (int i = 0; i < kDmaA; ++i) off_a[i] = piece_row[i] * (uint32_t)kRowBytes + piece_col[i];
+  auto issue = [&](int64_t tile, int st, uint32_t ring0) {
+    const uint32_t base = ring0 + (uint32_t)(st % kRing) * kStageBytes;
+    const int64_t kl = (int64_t)(((tile - t0) & 1) ? kStages - 1 - st : st) * kLine;
+    const uint8_t* b_base = B + tile * kTN * kRowBytes;
+    const uint32_t last = (uint32_t)min<int64_t>(kTN - 1, W - 1 - tile * kTN);
+#pragma unroll
+    for (int i = 0; i < kDmaPerWave; ++i)
+      dma16w((i < kDmaA ? a_base : b_base) + kl,
+             i < kDmaA ? off_a[i] : min(piece_row[i], last) * (uint32_t)kRowBytes + piece_col[i],
+             __builtin_amdgcn_readfirstlane(base + 1024 * (wave + kWaves * i)));
+  };
+  // The lane's operand of a 32-row block: two 16-byte chunks of its row (FP16:
+  // one per 16-K step, FP8: the two of its 32 codes).  swz() repeats every 16
+  // rows, so a block's first row adds only its own bytes.
+  const uint32_t at = chunk_pos(lane & 31, kFp8 ? 2 * (lane >> 5) : lane >> 5);
+  static_assert(32 % (kRowsPerBankRow * kChunks) == 0, "swz period");
+  struct Operand {
+    uint4 u[2];
+  };
+  auto product = [&](const Operand& x, const Operand& y, f32x16& c) {
+    if constexpr (!kFp8) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, x.u[ks]),
+                                                   __builtin_bit_cast(half8, y.u[ks]), c, 0, 0, 0);
+    } else {
+      // formats 0/0 = FP8 e4m3 for both operands; E8M0 scales 127 = 1.0
+      c = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(__builtin_bit_cast(i32x8, x),
+                                                           __builtin_bit_cast(i32x8, y), c, 0, 0, 0,
+                                                           127, 0, 127);
     }
   };
 
+  for (int u = 0; u < kRing - 1; ++u) issue(t0, u, ring_lds);
   for (int64_t tile = t0; tile < t1; ++tile) {
     f32x16 acc[2][kGN];
 #pragma unroll
@@ -385,144 +428,208 @@ __global__ __launch_bounds__(kThreads, 1) void score_wide_kernel(
       for (int g = 0; g < kGN; ++g)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[f][g][v] = 0.f;
-    float sj2[kGN];
+    // Each half of a stage's products (two of the wavefront's four window
+    // blocks) runs while the next half's operands are read from LDS.  One
+    // barrier per stage, before the first reads of stage st + 1: after it every
+    // wavefront's copies of stage st + 1 have landed and every wavefront holds
+    // all of stage st - 1, whose ring slot the copies of stage st + kRing - 1 take.
+    uint32_t at0 = at, ring0 = ring_lds;  // formed anew: addresses are not held over tiles
+    asm volatile("" : "+v"(at0), "+s"(ring0));
+    const uint32_t at1 = at0 ^ (kFp8 ? 16 : 32);
+    auto load = [&](int st, int row) {
+      const uint8_t* sb = &ring[st % kRing][0] + row * kLine;
+      return Operand{{*reinterpret_cast<const uint4*>(sb + at0),
+                      *reinterpret_cast<const uint4*>(sb + at1)}};
+    };
+    Operand a[2][2], b[kGN];
+    const int a_row = 64 * wr, b_row = kTM + 32 * kGN * wc;
+    wait_vm<(kRing - 2) * kDmaPerWave>();
+    __syncthreads();
+    a[0][0] = load(0, a_row);
+    a[0][1] = load(0, a_row + 32);
+    b[0] = load(0, b_row);
+    b[1] = load(0, b_row + 32);
+    // The copies run on into the next tile's first stages (past the chunk's last
+    // tile: that tile's again, never read).
+    const int64_t next = min(tile + 1, t1 - 1);
+    auto stage = [&](int st, auto parity, auto wraps, auto last) {
+      constexpr int u = decltype(parity)::value;
+      b[2] = load(st, b_row + 64);
+      b[3] = load(st, b_row + 96);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int g = 0; g < kGN; ++g) sj2[g] = 1.f;
-    if constexpr (kFp8) {
+      for (int g = 0; g < 2; ++g)
 #pragma unroll
-      for (int g = 0; g < kGN; ++g) {
-        const int64_t j = tile * kTN + 32 * kGN * wc + 32 * g + (lane & 31);
+        for (int f = 0; f < 2; ++f) product(a[u][f], b[g], acc[f][g]);
+      __builtin_amdgcn_sched_barrier(0);
+      wait_vm<(kRing - 3) * kDmaPerWave>();
+      __syncthreads();
+      if constexpr (decltype(wraps)::value) issue(next, st + kRing - 1 - kStages, ring0);
+      else issue(tile, st + kRing - 1, ring0);
+      if constexpr (!decltype(last)::value) {
+        a[u ^ 1][0] = load(st + 1, a_row);
+        a[u ^ 1][1] = load(st + 1, a_row + 32);
+        b[0] = load(st + 1, b_row);
+        b[1] = load(st + 1, b_row + 32);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int g = 2; g < 4; ++g)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) product(a[u][f], b[g], acc[f][g]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    const std::integral_constant<int, 0> even;
+    const std::integral_constant<int, 1> odd;
+    const std::false_type no;
+    const std::true_type yes;
+#pragma unroll 1
+    for (int st = 0; st < kStages - 4; st += 2) {
+      stage(st, even, no, no);
+      stage(st + 1, odd, no, no);
+    }
+    // (no branch in the loop: the compiler would move products over it and hold
+    // two stages' operands)
+    stage(kStages - 4, even, no, no);
+    stage(kStages - 3, odd, yes, no);
+    stage(kStages - 2, even, yes, no);
+    stage(kStages - 1, odd, yes, yes);
+    // the lane again, so that the epilogue's addresses are not formed before the
+    // loop and held through it
+    int el = lane;
+    asm volatile("" : "+v"(el));
+
+    // ---- epilogue.  Output element v of a 32x32 block is row 8(v/4) +
+    // 4(lane/32) + v%4, column lane%32; rows 2q and 2q+1 (v even, v+1) are a
+    // read's Re and Im.  A half of a wavefront compares its 128 scores of a read
+    // with the read's k-th best so far and hands those that are not below it, in
+    // any order, to the read's slots in LDS; the read's own wavefront then ranks
+    // them with the list.  If a half had more than kHitMax, the rest follow
+    // against the new k-th best.  The next tile's copies are under way meanwhile.
+    float sj2[kGN];  // FP8: squared scales of the lane's windows
+    uint32_t low[kGN];
+#pragma unroll
+    for (int g = 0; g < kGN; ++g) {
+      const int64_t j = tile * kTN + 32 * kGN * wc + 32 * g + (el & 31);
+      low[g] = 0xffffffffu - (uint32_t)j;
+      sj2[g] = 1.f;
+      if constexpr (kFp8) {
         const float sc = b_scale[min(j, W - 1)];
         sj2[g] = sc * sc;
       }
     }
-
-    // stages st .. st + kRing - 2 are in flight; one barrier per stage: after
-    // it every wavefront's copies of stage st have landed and every wavefront
-    // has finished reading stage st - 1, whose ring slot the copies of stage
-    // st + kRing - 1 then overwrite
+    const int64_t left = W - tile * kTN - 32 * kGN * wc - (el & 31);  // windows from the lane's first on
+    uint32_t done[2] = {0, 0};  // scores already handed over, per row block
+    __syncthreads();  // the slot's stage is read
+    for (bool more = true; more;) {
+      uint32_t count = 0;  // lane i of a half: of the half's i-th read
 #pragma unroll
-    for (int u = 0; u < kRing - 1; ++u) issue(tile, u);
-    for (int st = 0; st < kStages; ++st) {
-      if (st + kRing - 2 < kStages) wait_vm<(kRing - 2) * kDmaPerWave>(); else wait_vm<0>();
-      __syncthreads();
-      if (st + kRing - 1 < kStages) issue(tile, st + kRing - 1);
-      const uint8_t* sb = &ring[st % kRing][0];
-      if constexpr (!kFp8) {
-#pragma unroll
-        for (int ks = 0; ks < kLine / 32; ++ks) {
-          const int c = 2 * ks + (lane >> 5);  // this lane's 8 halves of the 16-K step
-          half8 a[2], b[kGN];
-#pragma unroll
-          for (int f = 0; f < 2; ++f) {
-            const int row = 64 * wr + 32 * f + (lane & 31);
-            a[f] = *reinterpret_cast<const half8*>(sb + chunk_pos(row, c));
-          }
-#pragma unroll
-          for (int g = 0; g < kGN; ++g) {
-            const int row = kTM + 32 * kGN * wc + 32 * g + (lane & 31);
-            b[g] = *reinterpret_cast<const half8*>(sb + chunk_pos(row, c));
-          }
-#pragma unroll
-          for (int f = 0; f < 2; ++f)
-#pragma unroll
-            for (int g = 0; g < kGN; ++g)
-              acc[f][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[f], b[g], acc[f][g], 0, 0, 0);
-        }
-      } else {
-#pragma unroll
-        for (int ks = 0; ks < kLine / 64; ++ks) {
-          const int c = 4 * ks + 2 * (lane >> 5);  // this lane's 32 codes of the 64-K step
-          i32x8 a[2], b[kGN];
-#pragma unroll
-          for (int f = 0; f < 2; ++f) {
-            const int row = 64 * wr + 32 * f + (lane & 31);
-            const uint4 u0 = *reinterpret_cast<const uint4*>(sb + chunk_pos(row, c));
-            const uint4 u1 = *reinterpret_cast<const uint4*>(sb + chunk_pos(row, c + 1));
-            a[f] = i32x8{(int)u0.x, (int)u0.y, (int)u0.z, (int)u0.w,
-                         (int)u1.x, (int)u1.y, (int)u1.z, (int)u1.w};
-          }
-#pragma unroll
-          for (int g = 0; g < kGN; ++g) {
-            const int row = kTM + 32 * kGN * wc + 32 * g + (lane & 31);
-            const uint4 u0 = *reinterpret_cast<const uint4*>(sb + chunk_pos(row, c));
-            const uint4 u1 = *reinterpret_cast<const uint4*>(sb + chunk_pos(row, c + 1));
-            b[g] = i32x8{(int)u0.x, (int)u0.y, (int)u0.z, (int)u0.w,
-                         (int)u1.x, (int)u1.y, (int)u1.z, (int)u1.w};
-          }
-          // formats 0/0 = FP8 e4m3 for both operands; E8M0 scales 127 = 1.0
-#pragma unroll
-          for (int f = 0; f < 2; ++f)
-#pragma unroll
-            for (int g = 0; g < kGN; ++g)
-              acc[f][g] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[f], b[g], acc[f][g], 0,
-                                                                           0, 0, 127, 0, 127);
-        }
-      }
-    }
-    __syncthreads();  // every wavefront is done with the ring before it becomes the F buffer
-
-    // ---- epilogue: F of every (read, window) of the tile into LDS.  Output
-    // element v of a 32x32 block is row 8(v/4) + 4(lane/32) + v%4, column
-    // lane%32; rows 2q and 2q+1 (v even, v+1) are a read's Re and Im.
-#pragma unroll
-    for (int f = 0; f < 2; ++f)
-#pragma unroll
-      for (int g = 0; g < kGN; ++g)
+      for (int f = 0; f < 2; ++f)
 #pragma unroll
         for (int v = 0; v < 16; v += 2) {
-          const int row = 64 * wr + 32 * f + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-          const int col = 32 * kGN * wc + 32 * g + (lane & 31);
-          const float re = acc[f][g][v], im = acc[f][g][v + 1];
-          float F = re * re + im * im;
-          if constexpr (kFp8) F *= sr2[f][v >> 1] * sj2[g];
-          Fbuf[(row >> 1) * kTN + col] = F;
-        }
-    __syncthreads();
-
-    // ---- per read: compare with the k-th best, insert the hits (wavefront w
-    // takes reads w, w + kWaves, ...; kTN / 64 windows per lane)
-    constexpr int kH = kTN / 64;
-    for (int rl = wave; rl < kTM / 2; rl += kWaves) {
-      const int64_t r = row0 / 2 + rl;
-      if (r >= n_reads) break;  // uniform
-      const uint64_t th = lists[rl][k_fetch - 1];
-      uint64_t key[kH], hit[kH], any = 0;
+          const int rl = (64 * wr + 32 * f + 8 * (v >> 2) + 4 * (el >> 5) + (v & 3)) >> 1;
+          // a key's high word is the score's bits + 1, an empty entry's 0
+          const uint32_t th = (uint32_t)(lists[rl][k_fetch - 1] >> 32);
+          const uint32_t least = th == 0 ? 0 : th - 1;
+          float sr2 = 1.f;  // FP8: squared scale of the read
+          if constexpr (kFp8) {
+            const float sc = a_scale[min(row0 / 2 + rl, (int64_t)n_reads - 1)];
+            sr2 = sc * sc;
+          }
+          uint32_t bits[kGN], top = 0;
 #pragma unroll
-      for (int h = 0; h < kH; ++h) {
-        const int col = lane + 64 * h;
-        const int64_t j = tile * kTN + col;
-        key[h] = j < W ? wide_key(Fbuf[rl * kTN + col], j) : 0;
-        hit[h] = __ballot(key[h] > th);
-        any |= hit[h];
-      }
-      if (any == 0) continue;
-      uint64_t cur = lane < k_fetch ? lists[rl][lane] : 0;
+          for (int g = 0; g < kGN; ++g) {
+            const float re = acc[f][g][v], im = acc[f][g][v + 1];
+            float F = re * re + im * im;
+            if constexpr (kFp8) F *= sr2 * sj2[g];
+            bits[g] = __float_as_uint(F);
+            top = max(top, bits[g]);
+          }
+          if (__ballot(top >= least) != 0) {
+            uint32_t n = 0;
 #pragma unroll
-      for (int h = 0; h < kH; ++h) {
-        uint64_t hits = hit[h];
-        while (hits != 0) {
-          const int src = __builtin_ctzll(hits);
-          hits &= hits - 1;
-          const uint64_t kn = __shfl(key[h], src, 64);
-          // position = entries that beat it; shift the rest down one lane
-          const int pos = __popcll(__ballot(lane < k_fetch && cur > kn));
-          if (pos >= k_fetch) continue;  // uniform
-          const uint64_t up = __shfl_up(cur, 1, 64);
-          cur = lane < pos ? cur : (lane == pos ? kn : up);
+            for (int g = 0; g < kGN; ++g) {
+              const uint32_t bit = 1u << (2 * v + g);
+              const bool hit = bits[g] >= least && 32 * g < left && (done[f] & bit) == 0;
+              const uint64_t m = __ballot(hit);
+              const uint32_t half = el < 32 ? (uint32_t)m : (uint32_t)(m >> 32);
+              const uint32_t slot = n + __popc(half & ((1u << (el & 31)) - 1));
+              n += __popc(half);
+              if (hit && slot < kHitMax) {
+                hits.key[rl][wc][slot] = ((uint64_t)(bits[g] + 1u) << 32) | low[g];
+                done[f] |= bit;
+              }
+            }
+            if ((el & 31) == 8 * f + v / 2) count = n;
+          }
         }
+      if ((el & 31) < 16) {
+        const int f = (el & 31) >> 3, v = 2 * (el & 7);
+        hits.count[(64 * wr + 32 * f + 8 * (v >> 2) + 4 * (el >> 5) + (v & 3)) >> 1][wc] = count;
       }
-      if (lane < k_fetch) lists[rl][lane] = cur;
+      __syncthreads();
+      const uint4 two = *reinterpret_cast<const uint4*>(&hits.count[2 * lane][0]);
+      more = __ballot(max(max(two.x, two.y), max(two.z, two.w)) > kHitMax) != 0;
+      // this wavefront's 16 reads
+      const int r_first = wave * (kTM / 2 / kWaves);
+      const uint2 mine = *reinterpret_cast<const uint2*>(&hits.count[r_first + (lane & 15)][0]);
+      uint64_t busy = __ballot((mine.x | mine.y) != 0) & 0xffff;
+      while (busy != 0) {
+        const int q = __builtin_ctzll(busy);
+        busy &= busy - 1;
+        const int n0 = min(__builtin_amdgcn_readlane((int)mine.x, q), kHitMax);
+        const int n1 = min(__builtin_amdgcn_readlane((int)mine.y, q), kHitMax);
+        uint64_t* list = lists[r_first + q];
+        // lanes 0..31 hold the list, 32..46 and 47..61 the hits; keys are
+        // distinct, and rank is the number of keys above the lane's
+        const int i = lane < 32 + kHitMax ? lane - 32 : lane - 32 - kHitMax;
+        const bool is_hit = lane >= 32 && (lane < 32 + kHitMax ? i < n0 : i < n1);
+        uint64_t key = 0;
+        if (lane < k_fetch) key = list[lane];
+        if (is_hit) key = hits.key[r_first + q][lane < 32 + kHitMax ? 0 : 1][i];
+        int rank = lane < k_fetch ? lane : k_fetch;
+        uint64_t todo = __ballot(is_hit);
+        while (todo != 0) {
+          const int src = __builtin_ctzll(todo);
+          todo &= todo - 1;
+          const uint64_t hit = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(key >> 32), src) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)key, src);
+          const int above = __popcll(__ballot(key > hit));
+          if (lane < k_fetch) rank += hit > key;
+          if (lane == src) rank = above;
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (rank < k_fetch) list[rank] = key;
+        __builtin_amdgcn_wave_barrier();
+      }
+      if (more) __syncthreads();  // lists and counts, before the next round
     }
-    __syncthreads();  // before the next tile's first stage overwrites Fbuf
+    __syncthreads();  // the hits are read before the next tile's copies reach their slot
   }
+  // the copies past the last tile have landed before the block's LDS is given back
+  wait_vm<0>();
+  __syncthreads();
 
-  // ---- the chunk's list of every read of the tile
+  // ---- the chunk's list of every read of the tile, for the merge and for the
+  // blocks that start later
+  if (tid < kTM / 2)
+    for (int i = 0; i < k_fetch; ++i)
+      if (lists[tid][i] == seed) lists[tid][i] = 0;
+  __syncthreads();
   for (int rl = wave; rl < kTM / 2; rl += kWaves) {
     const int64_t r = row0 / 2 + rl;
     if (r >= n_reads) break;
-    if (lane < k_fetch) part[(r * n_chunks + chunk) * k_fetch + lane] = lists[rl][lane];
+    if (lane < k_fetch)
+      __hip_atomic_store(&part[(r * n_chunks + chunk) * k_fetch + lane], lists[rl][lane],
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+}
+
+// Clears the last entry of every list.
+__global__ __launch_bounds__(256) void clear_wide_kernel(uint64_t* __restrict__ part, int64_t n_lists,
+                                                         int k_fetch) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n_lists) part[i * k_fetch + k_fetch - 1] = 0;
 }
 
 // One wavefront per read: the k_fetch best of its n_chunks lists (keys are
@@ -871,8 +978,8 @@ WidePlan plan_wide(int32_t n_reads, int64_t W) {
   if (c < 1) c = 1;
   p.chunk_tiles = (p.n_tiles + c - 1) / c;
   p.n_chunks = (int)((p.n_tiles + p.chunk_tiles - 1) / p.chunk_tiles);
-  p.n_quads = (p.n_chunks + kGroupChunks - 1) / kGroupChunks;
-  const int64_t groups = (int64_t)((p.n_rt + kGroupTiles - 1) / kGroupTiles) * p.n_quads;
+  const int64_t groups = (int64_t)((p.n_rt + kGroupTiles - 1) / kGroupTiles) *
+                         ((p.n_chunks + kGroupChunks - 1) / kGroupChunks);
   p.n_blocks = (groups + 7) / 8 * 8 * 32;  // whole rounds of 8 groups (idle blocks return)
   return p;
 }
@@ -922,10 +1029,13 @@ hipError_t launch_score_wide(const rm_index& idx, const void* read_emb, const fl
   uint64_t* part = static_cast<uint64_t*>(ws);
   auto kern = idx.p.precision == RM_FP8_E4M3 ? score_wide_kernel<RM_FP8_E4M3>
                                               : score_wide_kernel<RM_FP16>;
+  const int64_t n_lists = (int64_t)n_reads * p.n_chunks;
+  hipLaunchKernelGGL(clear_wide_kernel, dim3((unsigned)((n_lists + 255) / 256)), dim3(256), 0, st,
+                     part, n_lists, k_fetch);
   hipLaunchKernelGGL(kern, dim3((unsigned)p.n_blocks), dim3(kThreads), 0, st,
                      static_cast<const uint8_t*>(read_emb), read_scale, n_reads,
                      static_cast<const uint8_t*>(idx.d_emb), idx.d_scale, idx.n_windows, p.n_rt,
-                     p.n_tiles, p.chunk_tiles, p.n_chunks, p.n_quads, k_fetch, part);
+                     p.n_tiles, p.chunk_tiles, p.n_chunks, k_fetch, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(merge_wide_kernel, dim3((unsigned)(((int64_t)n_reads + 3) / 4)), dim3(256), 0,

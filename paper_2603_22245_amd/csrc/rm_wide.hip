@@ -783,6 +783,22 @@ struct CompSum {
   __device__ __forceinline__ float value() const { return hi + lo; }
 };
 
+// The FP32 value of a fixed-point sum.  FP64 holds sums up to 2^53 (2^13 letters)
+// exactly and takes a third of the conversion's instructions.
+__device__ __forceinline__ float from_fixed(unsigned long long u, bool fits53) {
+  if (!fits53) return (float)(long long)u * kFixUnit;
+  return (float)__builtin_fma((double)(int32_t)(u >> 32), 4294967296.0, (double)(uint32_t)u) *
+         kFixUnit;
+}
+
+// Sum over the aligned four lanes, in all of them; with zeros in the other lanes
+// the bits of wave_sum.
+__device__ __forceinline__ float quad_sum(float v) {
+  v += dpp<0xB1>(v);
+  v += dpp<0x4E>(v);
+  return v;
+}
+
 // Orders this wavefront's LDS accesses (a compiler barrier plus a wait on them);
 // no other wavefront is waited for.
 __device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); }
@@ -803,6 +819,14 @@ __device__ __forceinline__ void lds_order() { __builtin_amdgcn_fence(__ATOMIC_SE
 // and updates P_k and S by their changes (FP32, compensated sums).  Slot i of the candidate's
 // span in `pool` receives the key of start lo + i, 0 past the clamped
 // neighbourhood or for an invalid candidate.
+//
+// Bound by VALU issue: a slide works on m lanes, the leaving and the entering
+// token's change for each factor.  FOUR (m = 4: 256 classes, the most): the two
+// tokens' changes are formed side by side, in lanes 0..3 and 4..7, sums are of
+// one quad, and the fidelities of all starts are formed at once after the
+// slides.  20,000 reads x 32 candidates, radius 15, 256 classes: 7.5 ms,
+// 10.9 ms with the general path, whose bits these are.
+template <bool FOUR>
 __global__ __launch_bounds__(256) void refine_wide_kernel(
     const uint8_t* __restrict__ ref, int64_t W1, int N, int cstride, int64_t Wc, int s, int m,
     int n_class, const float2* __restrict__ phase32, const float4* __restrict__ step32,
@@ -862,7 +886,9 @@ __global__ __launch_bounds__(256) void refine_wide_kernel(
   // lanes k < m carry factor k: omega^f, and omega^(f T) (T = N - s + 1)
   const int G = n_class / kWC;  // lanes per factor; m * G = 64
   const bool fl = lane < m;
-  const float4 st = step32[fl ? lane : 0];
+  const int fk = FOUR ? lane & 3 : lane;  // this lane's factor
+  const float4 st = step32[fk < m ? fk : 0];
+  const bool fits53 = N <= 8192;
   const float2 fwd = make_float2(st.x, -st.y);             // omega^f
   const float2 adv = cmul(fwd, make_float2(st.z, st.w));  // omega^f omega^(f (N-s))
 
@@ -902,11 +928,11 @@ __global__ __launch_bounds__(256) void refine_wide_kernel(
     float pr = 0.f, pi = 0.f, sq = 0.f;
 #pragma unroll
     for (int q = 0; q < kWC; ++q) {
-      const float ur = (float)(long long)accR[acc_slot(kWC * lane + q)] * kFixUnit;
-      const float ui = (float)(long long)accI[acc_slot(kWC * lane + q)] * kFixUnit;
-      pr += xr[q] * ur + xi[q] * ui;
-      pi += xr[q] * ui - xi[q] * ur;
-      sq += ur * ur + ui * ui;
+      const float ur = from_fixed(accR[acc_slot(kWC * lane + q)], fits53);
+      const float ui = from_fixed(accI[acc_slot(kWC * lane + q)], fits53);
+      pr += __builtin_fmaf(xr[q], ur, xi[q] * ui);
+      pi += __builtin_fmaf(xr[q], ui, -(xi[q] * ur));
+      sq += __builtin_fmaf(ur, ur, ui * ui);
     }
     for (int d = 1; d < G; d <<= 1) {  // a factor's G lanes are contiguous and aligned
       pr += __shfl_xor(pr, d, 64);
@@ -926,6 +952,70 @@ __global__ __launch_bounds__(256) void refine_wide_kernel(
     const int out_c = tl < hi ? token_class(ref + tl, s, table) : kNoToken;
     const int in_c = tl < hi ? token_class(ref + tl + T, s, table) : kNoToken;
     uint64_t mine = 0;
+    if constexpr (FOUR) {
+      const bool enters = lane & 4, on = lane < 8 && fk < m;
+      // A sum of two products is rounded as in the general path: there the
+      // leaving token's, of negated phases, keep the first product's rounding
+      // and the entering token's the second's, so the leaving token's lanes take
+      // their operands imaginary part first.
+      const float* x = reinterpret_cast<const float*>(xs);
+      unsigned long long *acc0 = enters ? accR : accI, *acc1 = enters ? accI : accR;
+      float my_r = 0.f, my_i = 0.f, my_S = 0.f;  // lane i: of start lo + i
+      const int last = (int)(hi - lo);
+      for (int i = 0; i <= last; ++i) {
+        const float pr_i = Pr.value(), pi_i = Pi.value();
+        const float ipr = quad_sum(fl ? __builtin_fmaf(wt.x, pr_i, wt.y * pi_i) : 0.f);
+        const float ipi = quad_sum(fl ? __builtin_fmaf(wt.x, pi_i, -(wt.y * pr_i)) : 0.f);
+        const auto first = [](float v) {
+          return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+        };
+        const float s_r = first(ipr), s_i = first(ipi), s_S = first(S.value());
+        if (lane == i) {
+          my_r = s_r;
+          my_i = s_i;
+          my_S = s_S;
+        }
+        if (i == last) break;
+        const int oc = __builtin_amdgcn_readlane(out_c, i);
+        const int ic = __builtin_amdgcn_readlane(in_c, i);
+        const float2 in = cmul(wt, adv);
+        const float d0 = enters ? in.x : -wt.y, d1 = enters ? in.y : -wt.x;
+        const int cls = enters ? ic : oc;
+        float a = 0.f, b = 0.f, dS = 0.f;
+        if (on && cls >= 0 && cls < n_class) {
+          const int comp = fk * n_class + cls, sl = acc_slot(comp);
+          unsigned long long u0 = acc0[sl], u1 = acc1[sl];
+          if (enters && oc == ic) {  // after the leaving token's change
+            u0 += (unsigned long long)(long long)(-wt.x * kFixScale);
+            u1 += (unsigned long long)(long long)(-wt.y * kFixScale);
+          }
+          const float x0 = x[2 * comp + !enters], x1 = x[2 * comp + enters];
+          a = __builtin_fmaf(x0, d0, x1 * d1);
+          b = __builtin_fmaf(x0, d1, -(x1 * d0));
+          b = enters ? b : -b;
+          const float dx = enters ? d0 : d1, dy = enters ? d1 : d0;
+          dS = __builtin_fmaf(2.f,
+                              __builtin_fmaf(from_fixed(u0, fits53), d0, from_fixed(u1, fits53) * d1),
+                              __builtin_fmaf(dx, dx, dy * dy));
+          if (enters || oc != ic) {
+            acc0[sl] = u0 + (unsigned long long)(long long)(d0 * kFixScale);
+            acc1[sl] = u1 + (unsigned long long)(long long)(d1 * kFixScale);
+          }
+        }
+        // lanes 0..3 take the entering token's from lanes 4..7 (row_shl:4)
+        const float a_in = dpp<0x104>(a), b_in = dpp<0x104>(b), dS_in = dpp<0x104>(dS);
+        Pr.add(a);
+        Pr.add(a_in);
+        Pi.add(b);
+        Pi.add(b_in);
+        S.add(first(quad_sum(dS + dS_in)));
+        wt = cmul(wt, fwd);
+      }
+      const bool deg = xdeg || my_S < kDegenerateRel * N;
+      const float F = deg ? 0.f : __builtin_fmaf(my_r, my_r, my_i * my_i) / (X * my_S);
+      if (lane <= last) out[lane] = wide_key(F, lo + lane);
+      continue;
+    }
     for (int64_t t = lo; t <= hi; ++t) {
       // window t's components are omega^(-f_k (t - lo)) u: <x|c> = sum_k conj(wt_k) P_k
       const float pr_t = Pr.value(), pi_t = Pi.value(), S_t = S.value();
@@ -944,8 +1034,7 @@ __global__ __launch_bounds__(256) void refine_wide_kernel(
         auto change = [&](int cls, float2 d) {
           const int comp = lane * n_class + cls;
           const int sl = acc_slot(comp);
-          const float ur = (float)(long long)accR[sl] * kFixUnit;
-          const float ui = (float)(long long)accI[sl] * kFixUnit;
+          const float ur = from_fixed(accR[sl], fits53), ui = from_fixed(accI[sl], fits53);
           const float2 xv = xs[comp];
           Pr.add(xv.x * d.x + xv.y * d.y);
           Pi.add(xv.x * d.y - xv.y * d.x);
@@ -1063,7 +1152,8 @@ hipError_t launch_refine_wide(const rm_index& coarse, const uint8_t* ref, const 
   const int N = coarse.p.window_len;
   const int64_t W1 = coarse.ref_len - N + 1;  // step-1 windows
   uint64_t* pool = static_cast<uint64_t*>(ws);
-  hipLaunchKernelGGL(refine_wide_kernel, dim3((unsigned)n_reads), dim3(256), 0, st, ref, W1, N,
+  auto kern = coarse.p.n_freq == 4 ? refine_wide_kernel<true> : refine_wide_kernel<false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)n_reads), dim3(256), 0, st, ref, W1, N,
                      coarse.p.stride, coarse.n_windows,
                      coarse.p.mer_len > 1 ? coarse.p.mer_len : 1, coarse.p.n_freq,
                      kWideComplex / coarse.p.n_freq,

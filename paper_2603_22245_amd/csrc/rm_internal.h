@@ -224,28 +224,6 @@ __device__ __forceinline__ void direct_sum32(const uint8_t* __restrict__ str, in
   }
 }
 
-// Sine and cosine of z quarter turns: z = q + f with q the nearest integer (f
-// is exact), then the Taylor series in f on |f| <= 1/2, whose first left-out
-// terms are below 2e-9 (sine) and 2e-10 (cosine).
-__device__ __forceinline__ void sine_cosine(float z, float* sn, float* cs) {
-  const float q = rintf(z), f = z - q;
-  const float f2 = f * f;
-  float s = __builtin_fmaf(f2, 1.6044118e-4f, -4.6817541e-3f);
-  s = __builtin_fmaf(f2, s, 7.9692626e-2f);
-  s = __builtin_fmaf(f2, s, -6.4596410e-1f);
-  s = __builtin_fmaf(f2, s, 1.5707964f);
-  s *= f;
-  float c = __builtin_fmaf(f2, -2.5202042e-5f, 9.1926027e-4f);
-  c = __builtin_fmaf(f2, c, -2.0863481e-2f);
-  c = __builtin_fmaf(f2, c, 2.5366951e-1f);
-  c = __builtin_fmaf(f2, c, -1.2337006f);
-  c = __builtin_fmaf(f2, c, 1.f);
-  const int n = (int)q;
-  const float a = (n & 1) ? c : s, b = (n & 1) ? s : c;
-  *sn = __uint_as_float(__float_as_uint(a) ^ ((uint32_t)(n & 2) << 30));
-  *cs = __uint_as_float(__float_as_uint(b) ^ ((uint32_t)((n + 1) & 2) << 30));
-}
-
 // ---------------------------------------------------------------- launchers
 
 hipError_t launch_tables(const rm_params& p, double* phase64, float* phase32, float* step32,

@@ -89,6 +89,28 @@ __device__ __forceinline__ float relu(float x) {
   return __uint_as_float((uint32_t)max(__float_as_int(x), 0));
 }
 
+// Sine and cosine of z quarter turns: z = q + f with q the nearest integer (f
+// is exact), then the Taylor series in f on |f| <= 1/2, whose first left-out
+// terms are below 2e-9 (sine) and 2e-10 (cosine).
+__device__ __forceinline__ void sine_cosine(float z, float* sn, float* cs) {
+  const float q = rintf(z), f = z - q;
+  const float f2 = f * f;
+  float s = __builtin_fmaf(f2, 1.6044118e-4f, -4.6817541e-3f);
+  s = __builtin_fmaf(f2, s, 7.9692626e-2f);
+  s = __builtin_fmaf(f2, s, -6.4596410e-1f);
+  s = __builtin_fmaf(f2, s, 1.5707964f);
+  s *= f;
+  float c = __builtin_fmaf(f2, -2.5202042e-5f, 9.1926027e-4f);
+  c = __builtin_fmaf(f2, c, -2.0863481e-2f);
+  c = __builtin_fmaf(f2, c, 2.5366951e-1f);
+  c = __builtin_fmaf(f2, c, -1.2337006f);
+  c = __builtin_fmaf(f2, c, 1.f);
+  const int n = (int)q;
+  const float a = (n & 1) ? c : s, b = (n & 1) ? s : c;
+  *sn = __uint_as_float(__float_as_uint(a) ^ ((uint32_t)(n & 2) << 30));
+  *cs = __uint_as_float(__float_as_uint(b) ^ ((uint32_t)((n + 1) & 2) << 30));
+}
+
 // The three bfloat16 parts of eight values, packed in order.
 __device__ __forceinline__ void split8(const float (&x)[8], u32x4 (&part)[3]) {
 #pragma unroll
@@ -184,7 +206,11 @@ __device__ __forceinline__ void load_w2(const float* __restrict__ p, int L, int 
 // Phases of the lane's token (9-mer at `let`, its one-hot flanks x, location p): sine and cosine of
 // theta_k p + delta_k for its factors k - 1 = 16 ob + 4 g + v, index 4 ob + v.
 // k p is reduced mod N exactly: k p - q N is exact in FP32 (k p < 2^13; for an
-// N that FP32 does not hold, q = 0).
+// N that FP32 does not hold, q = 0).  The offset's whole turns are taken off
+// before it is rounded as quarter turns, whose constant is the sum of two FP32
+// values: the phase is off by at most 5e-7 (1e-7 root mean square) for offsets
+// up to 10^5 rad.  Scaled at once the offset alone would cost 4.4e-7 at 8 rad
+// and 1.0e-6 at 20, and the FP32 sum of both angles 2.8e-7 and 5.4e-7.
 __device__ __forceinline__ void token_phases(const float* __restrict__ params, const Net& net,
                                              const u32x4 (&w2)[2][2][3], int L, const uint8_t* let,
                                              const u32x4& x, int p, float Nf, float inv_n,
@@ -227,7 +253,10 @@ __device__ __forceinline__ void token_phases(const float* __restrict__ params, c
     for (int v = 0; v < 4; ++v) {
       const float kp = (float)(16 * ob + 4 * g + v + 1) * pf;
       const float r = __builtin_fmaf(-rintf(kp * inv_n), Nf, kp);
-      sine_cosine(__builtin_fmaf(r, turn, o[ob][v] * 0.63661977f), &sn[4 * ob + v], &cs[4 * ob + v]);
+      const float whole = 4.f * rintf(o[ob][v] * 0.15915494f);
+      const float part = __builtin_fmaf(o[ob][v], 2.5682553e-8f,
+                                        __builtin_fmaf(o[ob][v], 0.63661977f, -whole));
+      sine_cosine(__builtin_fmaf(r, turn, part), &sn[4 * ob + v], &cs[4 * ob + v]);
     }
 }
 

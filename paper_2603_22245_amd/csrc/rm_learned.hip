@@ -782,13 +782,10 @@ __global__ __launch_bounds__(kRedParams * kRedParts) void reduce_adam_kernel(
       red[1][q] = c;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-      float sum = red[0][0], pairs = red[1][0];
-      for (int r = 1; r < kRedParts; ++r) {
-        sum += red[0][r];
-        pairs += red[1][r];
-      }
-      *loss = pairs > 0.f ? sum / pairs : 0.f;
+    if (q == 0) {  // the sixteen parts as a tree: a running sum rounds its largest values most often
+      const float sum = wave_sum(tp < kRedParts ? red[0][tp] : 0.f);
+      const float pairs = wave_sum(tp < kRedParts ? red[1][tp] : 0.f);
+      if (tp == 0) *loss = pairs > 0.f ? sum / pairs : 0.f;
     }
     return;
   }

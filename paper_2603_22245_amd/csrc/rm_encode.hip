@@ -897,7 +897,7 @@ __global__ __launch_bounds__(256) void encode_reads_kernel(
 
 // Sine and cosine in FP64: x = q pi/2 + r with pi/2 as the sum of two FP64
 // values, then the Taylor series on |r| <= pi/4, whose first left-out terms are
-// below 5e-17 (sine) and 3e-18 (cosine).
+// below 5e-17 (sine) and 3e-18 (cosine).  |x| <= 10^9: q is held in 32 bits.
 __device__ __forceinline__ void sine_cosine64(double x, double* sn, double* cs) {
   const double q = rint(x * 0.63661977236758134308);
   double r = __builtin_fma(q, -1.5707963267948965580, x);
@@ -957,12 +957,15 @@ __device__ __forceinline__ void direct_sum_learned(const uint8_t* __restrict__ s
         e[u] = phase64[(int64_t)p * kM + k];
         d[u] = drow[(int64_t)p * 32 + k];
       }
+      const float most = fmaxf(fmaxf(fabsf(d[0]), fabsf(d[1])), fmaxf(fabsf(d[2]), fabsf(d[3])));
+      const bool far = __ballot(most > 1e9f) != 0;  // for the library's reduction
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int even = __builtin_amdgcn_readlane(mine, i0 + 2 * u);
         const int odd = __builtin_amdgcn_readlane(mine, i0 + 2 * u + 1);
         double sn, cs;
-        sine_cosine64((double)d[u], &sn, &cs);
+        if (far) sincos((double)d[u], &sn, &cs);
+        else sine_cosine64((double)d[u], &sn, &cs);
         const double er = e[u].x * cs - e[u].y * sn, ei = e[u].x * sn + e[u].y * cs;
         const double pr = partner64(er), pi = partner64(ei);
         const int own = h ? odd : even, other = h ? even : odd;

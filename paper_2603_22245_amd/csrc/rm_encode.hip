@@ -957,16 +957,29 @@ __device__ __forceinline__ void direct_sum_learned(const uint8_t* __restrict__ s
         e[u] = phase64[(int64_t)p * kM + k];
         d[u] = drow[(int64_t)p * 32 + k];
       }
+      double sn[4], cs[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) sine_cosine64((double)d[u], &sn[u], &cs[u]);
+      // angles past sine_cosine64's range: the library's, one after another, so
+      // that the rare path is one copy of it
       const float most = fmaxf(fmaxf(fabsf(d[0]), fabsf(d[1])), fmaxf(fabsf(d[2]), fabsf(d[3])));
-      const bool far = __ballot(most > 1e9f) != 0;  // for the library's reduction
+      if (__ballot(most > 1e9f) != 0) {
+#pragma unroll 1
+        for (int v = 0; v < 4; ++v) {
+          double s, c;
+          sincos((double)(v == 0 ? d[0] : v == 1 ? d[1] : v == 2 ? d[2] : d[3]), &s, &c);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            sn[u] = u == v ? s : sn[u];
+            cs[u] = u == v ? c : cs[u];
+          }
+        }
+      }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int even = __builtin_amdgcn_readlane(mine, i0 + 2 * u);
         const int odd = __builtin_amdgcn_readlane(mine, i0 + 2 * u + 1);
-        double sn, cs;
-        if (far) sincos((double)d[u], &sn, &cs);
-        else sine_cosine64((double)d[u], &sn, &cs);
-        const double er = e[u].x * cs - e[u].y * sn, ei = e[u].x * sn + e[u].y * cs;
+        const double er = e[u].x * cs[u] - e[u].y * sn[u], ei = e[u].x * sn[u] + e[u].y * cs[u];
         const double pr = partner64(er), pi = partner64(ei);
         const int own = h ? odd : even, other = h ? even : odd;
         a0.x += (own == L0) ? er : 0.0;

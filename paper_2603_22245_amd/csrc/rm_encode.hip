@@ -1013,6 +1013,7 @@ __device__ __forceinline__ void direct_sum_learned(const uint8_t* __restrict__ s
 // for the terms are exact in their own chunk and the state turns once in 16
 // slides).
 constexpr int kChunk = 16;
+static_assert(2 * kChunk == 32, "the chunk's tokens are a 32-bit mask");
 constexpr int kLearnedBlocks = 4;  // resident blocks per CU
 
 template <int PREC>
@@ -1076,9 +1077,21 @@ __global__ __launch_bounds__(256, kLearnedBlocks) void encode_reference_learned_
       d[q] = delta[(s0 + tb + i + (row >= kChunk ? N - 8 : 0)) * 32 + (lane & 31)];
     }
     // their letters' pair: leaving ref[s0+t+4], entering ref[s0+t+N-4]
-    int pair = 24;
-    if (lane < cnt)
-      pair = 5 * min((int)ref[s0 + tb + lane + 4], 4) + min((int)ref[s0 + tb + lane + N - 4], 4);
+    int leaves = 4, enters = 4;
+    if (lane < cnt) {
+      leaves = min((int)ref[s0 + tb + lane + 4], 4);
+      enters = min((int)ref[s0 + tb + lane + N - 4], 4);
+    }
+    const int pair = 5 * leaves + enters;
+    // A token of another letter has no term: its offsets may hold anything, and
+    // what multiplies it by zero below has to be a number.
+    const uint32_t none = (uint32_t)__ballot(lane < cnt && leaves == 4) |
+                          (uint32_t)__ballot(lane < cnt && enters == 4) << kChunk;
+    if (none != 0) {
+#pragma unroll
+      for (int q = 0; q < kChunk; ++q)
+        if (none >> (2 * q + (lane >> 5)) & 1) d[q] = 0.f;
+    }
 #pragma unroll
     for (int q = 0; q < kChunk; ++q) {
       const int row = 2 * q + (lane >> 5);

@@ -195,7 +195,8 @@ size_t rm_read_emb_bytes(int32_t n_reads, const rm_params* p);
 int rm_encode_reads(const rm_index* idx, const uint8_t* d_seq, const int64_t* d_off,
                     int32_t n_reads, void* d_read_emb, float* d_read_scale, void* stream);
 
-/* Bytes of the workspace rm_score_topk needs. 0 if invalid. */
+/* Bytes of a workspace for rm_score_topk with n_reads reads or fewer. 0 if
+ * invalid. */
 size_t rm_score_workspace_bytes(const rm_index* idx, int32_t n_reads, int32_t k_fetch);
 
 /* Score every read against every window and keep, per read, the k_fetch best
@@ -218,15 +219,15 @@ int rm_score_topk(const rm_index* idx, const void* d_read_emb, const float* d_re
  * capture, tight serving loops, harnesses that forbid allocation).  The same
  * call as rm_score_topk, with its workspace in a device array the library
  * owns: RM_NOALLOC_SCRATCH_BYTES per GPU, held from the first call on that GPU
- * until the process ends (enough for rm_score_workspace_bytes of 100,000
- * reads against 10^7 windows with 16 candidates).  The array of the CURRENT
+ * until the process ends (enough for 100,000 reads against 10^7 windows with 8
+ * candidates, or 60,000 with 16).  The array of the CURRENT
  * device is used, so call it with the stream's device current.  Its device
  * address is looked up on the first call on each device; no call allocates or
  * frees memory.  Every call on one GPU shares that GPU's array: calls that
  * overlap in time on one GPU (other streams, other host threads) race and
  * must be serialised by the caller; each call clears what must start at zero.
- * Errors: as rm_score_topk; RM_ESIZE also when rm_score_workspace_bytes
- * exceeds RM_NOALLOC_SCRATCH_BYTES; RM_EHIP if the array's address cannot be
+ * Errors: as rm_score_topk; RM_ESIZE also when the call's reads
+ * need more than RM_NOALLOC_SCRATCH_BYTES; RM_EHIP if the array's address cannot be
  * found; RM_EUNSUPPORTED for a device index of 64 or more. */
 #define RM_NOALLOC_SCRATCH_BYTES ((size_t)256 << 20)
 int rm_score_topk_noalloc(const rm_index* idx, const void* d_read_emb, const float* d_read_scale,
@@ -444,8 +445,9 @@ typedef struct rm_tuning {
 int rm_bucket_reads(const int64_t* h_off, int32_t n_reads, const int32_t* bucket_len,
                     int32_t n_buckets, int32_t* h_bucket, int32_t* h_count);
 
-/* Workspace bytes of rm_score_topk_groups; 0 if invalid.  idx and n_reads are
- * host arrays of n_groups entries; tune may be NULL. */
+/* Workspace bytes of rm_score_topk_groups with at most n_reads[i] reads in group i;
+ * 0 if invalid.  idx and n_reads are host arrays of n_groups entries; tune may be
+ * NULL. */
 size_t rm_score_groups_workspace_bytes(const rm_index* idx, int32_t n_groups,
                                        const int32_t* n_reads, int32_t k_fetch,
                                        const rm_tuning* tune);

@@ -144,6 +144,16 @@ int noalloc_scratch(void** out) {
 
 }  // namespace
 
+// plan_score or score_workspace_bytes of checked groups.
+template <typename Plan>
+static auto groups_plan(Plan plan, const rm_index* idx, int32_t n_groups, const int32_t* n_reads,
+                        int32_t k_fetch, const rm_tuning* tune) {
+  int64_t W[RM_MAX_GROUPS];
+  for (int i = 0; i < n_groups; ++i) W[i] = idx[i].n_windows;
+  rm::Tuning t{tune ? tune->read_tile : 0, tune ? tune->chunk_tiles : 0};
+  return plan(idx[0].p.precision, n_groups, W, n_reads, k_fetch, t);
+}
+
 extern "C" {
 
 const char* rm_status_str(int status) {
@@ -324,7 +334,11 @@ int rm_score_topk_noalloc(const rm_index* idx, const void* d_read_emb, const flo
   if (need == 0)  // invalid arguments: rm_score_topk names the error and enqueues nothing
     return rm_score_topk(idx, d_read_emb, d_read_scale, n_reads, k_fetch, d_cand_idx,
                          d_cand_score, reinterpret_cast<void*>(kNoallocAlign), 0, stream);
-  if (need > (size_t)RM_NOALLOC_SCRATCH_BYTES) return RM_ESIZE;
+  // what this call's reads need, which may be less than what serves fewer as well
+  const size_t own = wide_encoding(&idx->p)
+                         ? need
+                         : groups_plan(rm::plan_score, idx, 1, &n_reads, k_fetch, nullptr).ws_bytes;
+  if (own > (size_t)RM_NOALLOC_SCRATCH_BYTES) return RM_ESIZE;
   void* ws = nullptr;
   const int st = noalloc_scratch(&ws);
   if (st != RM_OK) return st;
@@ -542,20 +556,11 @@ static int groups_ok(const rm_index* idx, int32_t n_groups, const int32_t* n_rea
   return RM_OK;
 }
 
-static rm::ScorePlan groups_plan(const rm_index* idx, int32_t n_groups, const int32_t* n_reads,
-                                 int32_t k_fetch, const rm_tuning* tune) {
-  int64_t W[RM_MAX_GROUPS];
-  for (int i = 0; i < n_groups; ++i) W[i] = idx[i].n_windows;
-  rm::Tuning t{tune ? tune->read_tile : 0, tune ? tune->chunk_tiles : 0};
-  return rm::plan_score(idx[0].p.precision, n_groups, W, n_reads, k_fetch, t);
-}
-
 size_t rm_score_groups_workspace_bytes(const rm_index* idx, int32_t n_groups,
                                        const int32_t* n_reads, int32_t k_fetch,
                                        const rm_tuning* tune) {
   if (groups_ok(idx, n_groups, n_reads, k_fetch) != RM_OK) return 0;
-  rm::ScorePlan plan = groups_plan(idx, n_groups, n_reads, k_fetch, tune);
-  return plan.ok ? plan.ws_bytes : 0;
+  return groups_plan(rm::score_workspace_bytes, idx, n_groups, n_reads, k_fetch, tune);
 }
 
 int rm_score_topk_groups(const rm_index* idx, int32_t n_groups, const void* const* d_read_emb,
@@ -575,7 +580,7 @@ int rm_score_topk_groups(const rm_index* idx, int32_t n_groups, const void* cons
   if (tune && (tune->chunk_tiles < 0 ||
                (tune->read_tile != 0 && tune->read_tile != 128 && tune->read_tile != 256)))
     return RM_EUNSUPPORTED;
-  rm::ScorePlan plan = groups_plan(idx, n_groups, n_reads, k_fetch, tune);
+  rm::ScorePlan plan = groups_plan(rm::plan_score, idx, n_groups, n_reads, k_fetch, tune);
   if (!plan.ok) return tune && tune->read_tile ? RM_EUNSUPPORTED : RM_ESIZE;
   if (ws_bytes < plan.ws_bytes) return RM_ESIZE;
   return hip_status(rm::launch_score_topk(idx, plan, d_read_emb, d_read_scale, n_reads, k_fetch,

@@ -301,7 +301,7 @@ struct ScorePlan {
   GroupPlan g[kMaxGroups];
   int64_t total_items;
   size_t counter_offset;
-  size_t ws_bytes;
+  size_t ws_bytes;  // of this launch
   bool ok;
 };
 
@@ -310,6 +310,10 @@ bool read_tile_ok(int precision, int kp, int read_tile);
 
 ScorePlan plan_score(int precision, int n_groups, const int64_t* W, const int32_t* R, int k_fetch,
                      Tuning t);
+// Bytes that serve every launch of at most R[i] reads in group i; 0 if the plan
+// is not ok.
+size_t score_workspace_bytes(int precision, int n_groups, const int64_t* W, const int32_t* R,
+                             int k_fetch, Tuning t);
 
 hipError_t launch_score_topk(const rm_index* idx, const ScorePlan& plan,
                              const void* const* read_emb, const float* const* read_scale,

@@ -26,10 +26,12 @@ __global__ void clear_state(ScoreLaunch L) {
 
 // Keys per read that merge_kernel takes, and that merge_block_kernel takes.
 constexpr int kMergeKeys = 1024, kMergeKeysWide = 16384;
-// One block per CU of the chip; the items of a launch with few read tiles;
-// the reads of a single group up to which read tiles hold 128.
-constexpr int64_t kChipBlocks = 256, kMaxItems = 8 * kChipBlocks;
+// One block per CU of the chip; the reads of a single group up to which read
+// tiles hold 128.
+constexpr int64_t kChipBlocks = 256;
 constexpr int32_t kFewReads = 1024;
+// Reads up to which a launch only streams the index.
+constexpr int32_t kStreamReads = 32;
 
 // Merge the P per-chunk lists of each read into its k_fetch best (keys are
 // unique per read).  One wavefront per read (all its lanes active): each lane
@@ -242,20 +244,89 @@ bool read_tile_ok(int precision, int kp, int read_tile) {
 
 static size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
+// Reads of a block tile where the caller names none.  128-read tiles leave room
+// for two blocks per CU and lose less to a part-filled tile: up to 1,024 reads
+// they are the faster ones (FP16, 200 reads x 20,000 windows 101 -> 86 us, 1,000
+// x 100,000 238 -> 225 us, 100 x 10^7 1.18 -> 1.11 ms), beyond that the wider
+// tile's reuse of each window is (2,000 x 10^6: 1.79 against 1.84 ms).
+static int default_read_tile(int precision, int kp, int n_groups, int64_t R0) {
+  const bool few = n_groups == 1 && R0 <= kFewReads;
+  return !few && read_tile_ok(precision, kp, 256) ? 256 : 128;
+}
+
+// A group's read tiles.  256-read tiles run two fragments per wavefront; a group
+// that would leave a quarter or more of its padded reads empty takes 128-read
+// tiles (one fragment per wavefront, half the work per tile) in the same launch.
+static void tile_reads(int64_t R, int rt, GroupPlan& gp) {
+  gp.read_tiles = (int)((R + rt - 1) / rt);
+  gp.thin = 0;
+  if (rt == 256) {
+    const int64_t t128 = (R + 127) / 128;
+    if (4 * 128 * t128 <= 3 * 256 * (int64_t)gp.read_tiles) {
+      gp.thin = 1;
+      gp.read_tiles = (int)t128;
+    }
+  }
+}
+
+// A group's chunks, with chunk_tiles 64-window units per chunk or the default
+// rule (<= 0).  share: the group's part of kChipBlocks by its work.
+static void cut_windows(int64_t R, int64_t tiles, int64_t chunk_tiles, int64_t share, bool only,
+                        int kp, GroupPlan& gp) {
+  int64_t ct = chunk_tiles, most = kMergeKeys / kp;
+  if (ct <= 0) {
+    // about 30 items per CU of a 256-CU chip (a short last round), at least
+    // 64 tile units each, at most 1024 keys per read for the merge; fewer,
+    // longer items leave an uneven last round, more items repeat each
+    // read's top-k warm-up in more chunks
+    int64_t P = (kChipBlocks * 30 + gp.read_tiles - 1) / gp.read_tiles;
+    P = std::min({P, (tiles + 63) / 64, most});
+    // Few read tiles: that rule gives 64 chunks of 16-key lists at most,
+    // and one per 4,096 windows (10 items for 200 FP32 reads against
+    // 20,000 windows).  Here a group gets its share of eight items per CU
+    // with chunks of 2,048 windows or more, but at least its share of one
+    // per CU, and a single group fills whole rounds of the chip.  Measured
+    // (chunks before -> now): FP32 200 x 20,000 1,330 -> 165 us (5 -> 104),
+    // FP16 8 x 10^7 2,310 -> 725 us (64 -> 512), 300 x 10^6 970 -> 440 us.
+    // Up to 32 reads the launch only streams the index, and shorter
+    // chunks cost more than they balance (8 x 10^7: 512 chunks 724 us,
+    // 1,024 775 us).
+    most = std::max<int64_t>(most, kMergeKeysWide / kp);
+    int64_t Q = std::min(8 * share / gp.read_tiles, (tiles + 31) / 32);
+    Q = std::max(Q, (share + gp.read_tiles - 1) / gp.read_tiles);
+    if (R <= kStreamReads) Q = std::min<int64_t>(Q, 2 * kChipBlocks);
+    if (only) {
+      const int64_t rounds = (Q * gp.read_tiles + kChipBlocks - 1) / kChipBlocks;
+      Q = std::max(Q, rounds * kChipBlocks / gp.read_tiles);
+    }
+    P = std::max(P, std::min({Q, most, tiles}));
+    P = std::max<int64_t>(P, 1);
+    ct = (tiles + P - 1) / P;
+  }
+  if (ct < 1) ct = 1;
+  int64_t P = (tiles + ct - 1) / ct;
+  if (P > most) {  // keep the merge within its keys per read
+    P = most;
+    ct = (tiles + P - 1) / P;
+    P = (tiles + ct - 1) / ct;
+  }
+  gp.chunk_windows = ct * kPlanW;
+  gp.chunks = (int)P;
+}
+
+static int list_keys(int k_fetch) {
+  return k_fetch <= 8 ? 8 : k_fetch <= 16 ? 16 : k_fetch <= 32 ? 32 : 64;
+}
+
+static size_t list_bytes(int64_t lists, int kp) {
+  return align256((size_t)lists * (size_t)kp * sizeof(uint64_t));
+}
+
 ScorePlan plan_score(int precision, int n_groups, const int64_t* W, const int32_t* R, int k_fetch,
                      Tuning t) {
   ScorePlan p{};
-  p.kp = k_fetch <= 8 ? 8 : k_fetch <= 16 ? 16 : k_fetch <= 32 ? 32 : 64;
-  int rt = t.read_tile;
-  if (rt == 0) {
-    // 128-read tiles leave room for two blocks per CU and lose less to a
-    // part-filled tile: up to 1,024 reads they are the faster ones (FP16, 200
-    // reads x 20,000 windows 101 -> 86 us, 1,000 x 100,000 238 -> 225 us, 100
-    // x 10^7 1.18 -> 1.11 ms), beyond that the wider tile's reuse of each
-    // window is (2,000 x 10^6: 1.79 against 1.84 ms)
-    const bool few = n_groups == 1 && R[0] <= kFewReads;
-    rt = !few && read_tile_ok(precision, p.kp, 256) ? 256 : 128;
-  }
+  p.kp = list_keys(k_fetch);
+  const int rt = t.read_tile ? t.read_tile : default_read_tile(precision, p.kp, n_groups, R[0]);
   if (!read_tile_ok(precision, p.kp, rt) || n_groups < 1 || n_groups > kMaxGroups) return p;
   p.read_tile = rt;
   p.n_groups = n_groups;
@@ -263,18 +334,7 @@ ScorePlan plan_score(int precision, int n_groups, const int64_t* W, const int32_
   int64_t work[kMaxGroups], total_work = 0;
   for (int i = 0; i < n_groups; ++i) {
     GroupPlan& gp = p.g[i];
-    gp.read_tiles = (int)(((int64_t)R[i] + rt - 1) / rt);
-    // 256-read tiles run two fragments per wavefront; a group that would leave
-    // a quarter or more of its padded reads empty takes 128-read tiles (one
-    // fragment per wavefront, half the work per tile) in the same launch
-    gp.thin = 0;
-    if (rt == 256) {
-      const int64_t t128 = ((int64_t)R[i] + 127) / 128;
-      if (4 * 128 * t128 <= 3 * 256 * (int64_t)gp.read_tiles) {
-        gp.thin = 1;
-        gp.read_tiles = (int)t128;
-      }
-    }
+    tile_reads(R[i], rt, gp);
     work[i] = (W[i] + kPlanW - 1) / kPlanW * gp.read_tiles * (rt == 256 && !gp.thin ? 2 : 1);
     total_work += work[i];
   }
@@ -282,67 +342,68 @@ ScorePlan plan_score(int precision, int n_groups, const int64_t* W, const int32_
   int64_t items = 0;
   for (int i = 0; i < n_groups; ++i) {
     GroupPlan& gp = p.g[i];
-    const int64_t tiles = (W[i] + kPlanW - 1) / kPlanW;
-    int64_t ct = t.chunk_tiles, most = kMergeKeys / p.kp;
-    if (ct <= 0) {
-      // about 30 items per CU of a 256-CU chip (a short last round), at least
-      // 64 tile units each, at most 1024 keys per read for the merge; fewer,
-      // longer items leave an uneven last round, more items repeat each
-      // read's top-k warm-up in more chunks
-      int64_t P = (kChipBlocks * 30 + gp.read_tiles - 1) / gp.read_tiles;
-      P = std::min({P, (tiles + 63) / 64, most});
-      // Few read tiles: that rule gives 64 chunks of 16-key lists at most,
-      // and one per 4,096 windows (10 items for 200 FP32 reads against
-      // 20,000 windows).  Here a group gets its share of eight items per CU
-      // with chunks of 2,048 windows or more, but at least its share of one
-      // per CU, and a single group fills whole rounds of the chip.  Measured
-      // (chunks before -> now): FP32 200 x 20,000 1,330 -> 165 us (5 -> 104),
-      // FP16 8 x 10^7 2,310 -> 725 us (64 -> 512), 300 x 10^6 970 -> 440 us.
-      // Up to 32 reads the launch only streams the index, and shorter
-      // chunks cost more than they balance (8 x 10^7: 512 chunks 724 us,
-      // 1,024 775 us).
-      most = std::max<int64_t>(most, kMergeKeysWide / p.kp);
-      const int64_t share = (work[i] * kChipBlocks + total_work - 1) / total_work;
-      int64_t Q = std::min(8 * share / gp.read_tiles, (tiles + 31) / 32);
-      Q = std::max(Q, (share + gp.read_tiles - 1) / gp.read_tiles);
-      if (R[i] <= 32) Q = std::min<int64_t>(Q, 2 * kChipBlocks);
-      if (n_groups == 1) {
-        const int64_t rounds = (Q * gp.read_tiles + kChipBlocks - 1) / kChipBlocks;
-        Q = std::max(Q, rounds * kChipBlocks / gp.read_tiles);
-      }
-      P = std::max(P, std::min({Q, most, tiles}));
-      P = std::max<int64_t>(P, 1);
-      ct = (tiles + P - 1) / P;
-    }
-    if (ct < 1) ct = 1;
-    int64_t P = (tiles + ct - 1) / ct;
-    if (P > most) {  // keep the merge within its keys per read
-      P = most;
-      ct = (tiles + P - 1) / P;
-      P = (tiles + ct - 1) / ct;
-    }
-    gp.chunk_windows = ct * kPlanW;
-    gp.chunks = (int)P;
+    cut_windows(R[i], (W[i] + kPlanW - 1) / kPlanW, t.chunk_tiles,
+                (work[i] * kChipBlocks + total_work - 1) / total_work, n_groups == 1, p.kp, gp);
     gp.lists_offset = off;
-    int64_t keys = (int64_t)R[i] * P;
-    // A default plan's chunks times read tiles stay within kMaxItems (or the
-    // windows' own units), whatever the reads: room for that many keeps the
-    // workspace of more reads large enough for fewer.
-    if (t.chunk_tiles <= 0)
-      keys = std::max(keys, (R[i] <= kFewReads ? 128 : rt) *
-                                std::min(kMaxItems, std::max(2 * kChipBlocks, tiles)));
-    off = align256(off + (size_t)keys * (size_t)p.kp * sizeof(uint64_t));
+    off += list_bytes((int64_t)R[i] * gp.chunks, p.kp);
     gp.thr_offset = off;
     off = align256(off + (size_t)R[i] * sizeof(uint32_t));
     gp.slot_offset = off;
     off = align256(off + (size_t)R[i] * kScoreSlots * sizeof(uint64_t));
-    items += (int64_t)gp.read_tiles * P;
+    items += (int64_t)gp.read_tiles * gp.chunks;
   }
   p.counter_offset = off;
   p.ws_bytes = off + 256;
   p.total_items = items;
   p.ok = items > 0 && items < INT32_MAX;
   return p;
+}
+
+// What every launch of at most these reads needs.  The default rule gives fewer
+// reads more chunks, so a plan of its own reads alone would be too small for some
+// smaller batches (FP16, 20,000 windows, 16 candidates: 14,114 reads 18.1 MB,
+// 13,372 reads 18.8 MB).
+size_t score_workspace_bytes(int precision, int n_groups, const int64_t* W, const int32_t* R,
+                             int k_fetch, Tuning t) {
+  const ScorePlan p = plan_score(precision, n_groups, W, R, k_fetch, t);
+  if (!p.ok) return 0;
+  if (t.chunk_tiles > 0) return p.ws_bytes;  // chunks of a given length: as many for any reads
+  // The most lists of a group over its smaller read counts.  Chunks change with
+  // the read tiles only, so the counts that matter are the last of each.  From
+  // kChipBlocks * 30 tiles on there is one chunk.
+  int64_t sum = 0;
+  size_t rest = 256, lists = 0;
+  for (int i = 0; i < n_groups; ++i) {
+    const int64_t tiles = (W[i] + kPlanW - 1) / kPlanW;
+    int64_t most = 0;
+    const auto at = [&](int64_t r) {
+      GroupPlan g{};
+      tile_reads(r, t.read_tile ? t.read_tile : default_read_tile(precision, p.kp, n_groups, r), g);
+      cut_windows(r, tiles, 0, kChipBlocks, n_groups == 1, p.kp, g);
+      most = std::max(most, r * g.chunks);
+    };
+    at(std::min<int64_t>(R[i], kStreamReads));
+    for (int64_t r = 128; r < std::min<int64_t>(R[i], kChipBlocks * 30 * 256 + 1); r += 128) at(r);
+    at(R[i]);
+    sum += most;
+    lists += list_bytes(most, p.kp);
+    rest += align256((size_t)R[i] * sizeof(uint32_t)) +
+            align256((size_t)R[i] * kScoreSlots * sizeof(uint64_t));
+  }
+  if (n_groups > 1) {
+    // The groups share the chip: a group with share s has at most 8 s tiles' worth
+    // of lists (or a list a read), and the shares add up to kChipBlocks and one
+    // for each group; besides these at most those of the 30 items per CU.
+    int64_t shared = 8 * (kChipBlocks + n_groups) * p.read_tile;
+    for (int i = 0; i < n_groups; ++i) {
+      const int64_t chunks = std::min<int64_t>((W[i] + 64 * kPlanW - 1) / (64 * kPlanW),
+                                               kMergeKeys / p.kp);
+      shared += R[i] + std::min<int64_t>(R[i] * std::max<int64_t>(chunks, 1),
+                                         kChipBlocks * 30 * p.read_tile + R[i]);
+    }
+    if (shared < sum) lists = list_bytes(shared, p.kp) + 256 * (size_t)n_groups;
+  }
+  return lists + rest;
 }
 
 hipError_t launch_score_topk(const rm_index* idx, const ScorePlan& plan,

@@ -19,6 +19,8 @@
 // about 10^5 pairs on.  Pairs of 150 letters: 8,192 in 30 us, 10^6 in 0.94 ms
 // (126 us and 4.5 ms with a lane per pair); of 16 letters: 10^6 in 39 us (44 us
 // with a lane per pair, 187 us with four lanes for patterns of one word).
+#include <algorithm>
+
 #include "rm_internal.h"
 
 namespace rm {
@@ -154,9 +156,16 @@ __global__ __launch_bounds__(64 * kWords) void levenshtein_kernel(
 
 hipError_t launch_levenshtein(const uint8_t* a, const int64_t* aoff, const uint8_t* b,
                               const int64_t* boff, int64_t n, int32_t* out, hipStream_t s) {
-  hipLaunchKernelGGL(levenshtein_kernel, dim3((unsigned)((n + kPairs - 1) / kPairs)),
-                     dim3(64 * kWords), 0, s, a, aoff, b, boff, n, out);
-  return hipGetLastError();
+  // a launch has fewer than 2^32 threads, four per pair
+  constexpr int64_t kMost = (int64_t)1 << 29;
+  for (int64_t i = 0; i < n; i += kMost) {
+    const int64_t some = std::min(n - i, kMost);
+    hipLaunchKernelGGL(levenshtein_kernel, dim3((unsigned)((some + kPairs - 1) / kPairs)),
+                       dim3(64 * kWords), 0, s, a, aoff + i, b, boff + i, some, out + i);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace rm

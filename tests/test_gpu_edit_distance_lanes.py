@@ -1,5 +1,6 @@
 """The edit-distance kernel's blocks of 64 pairs with one, two or four lanes a pair:
-exact against the oracle's dynamic programme."""
+exact against the oracle's dynamic programme, and more pairs than one launch has
+threads for."""
 import numpy as np
 import pytest
 
@@ -42,3 +43,20 @@ def test_blocks_by_longest_pattern(n, shortest, longest, text):
     want[[min(len(x), len(y)) > 256 for x, y in zip(a, b)]] = -1
     got = learned.levenshtein(learned.upload_pairs(*_pack(a), *_pack(b))).cpu().numpy()
     np.testing.assert_array_equal(got, want)
+
+
+def test_more_pairs_than_a_launch_has_threads():
+    """2^30 + 101 pairs of an empty string and one of one or two letters: four
+    threads a pair would be more than 2^32."""
+    torch = torch_cuda()
+    from paper_2603_22245_amd import _lib as L
+    n = (1 << 30) + 101
+    b_off = torch.arange(n + 1, dtype=torch.int64, device="cuda").mul_(3).div_(2, rounding_mode="floor")
+    a_off = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    b = torch.zeros(int(b_off[-1]), dtype=torch.uint8, device="cuda")
+    out = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    L.rm_levenshtein(b, a_off, b, b_off, n, out)
+    torch.cuda.synchronize()
+    for i in range(0, n, 1 << 28):
+        j = min(n, i + (1 << 28))
+        assert torch.equal(out[i:j].long(), b_off[i + 1:j + 1] - b_off[i:j])

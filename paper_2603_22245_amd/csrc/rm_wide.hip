@@ -312,7 +312,8 @@ __device__ __forceinline__ uint32_t chunk_pos(int row, int c) {
 // from the largest k-th best of its reads' chunks that are done: what does not
 // beat it is not among the read's k best.  (Any value it finds there, a chunk's
 // k-th best or the 0 that the entries are cleared to, is a lower bound, so the
-// result does not depend on which chunks are done.)  A chunk of 31,000 windows
+// result does not depend on which chunks are done; n_seeds is the number of
+// chunks, or 0 where the entries are not cleared and not read.)  A chunk of 31,000 windows
 // ranks about 250 keys a read from an empty list and 30 from another's k-th best.
 //
 // FP16: 32x32x16 MFMAs, F = Re^2 + Im^2.  FP8: 32x32x64 MFMAs on the e4m3
@@ -322,7 +323,7 @@ template <int PREC>
 __global__ __launch_bounds__(kThreads, 1) void score_wide_kernel(
     const uint8_t* __restrict__ A, const float* __restrict__ a_scale, int32_t n_reads,
     const uint8_t* __restrict__ B, const float* __restrict__ b_scale, int64_t W,
-    int n_rt, int64_t n_tiles, int64_t chunk_tiles, int n_chunks, int k_fetch,
+    int n_rt, int64_t n_tiles, int64_t chunk_tiles, int n_chunks, int n_seeds, int k_fetch,
     uint64_t* __restrict__ part) {
   // the stage ring; between tiles its last slot takes the tile's hits
   __shared__ __attribute__((aligned(1024))) uint8_t ring[kRing][kStageBytes];
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(kThreads, 1) void score_wide_kernel(
     const int64_t r = row0 / 2 + tid;
     if (r < n_reads) {
       seed = 0;
-      for (int c = 0; c < n_chunks; ++c)
+      for (int c = 0; c < n_seeds; ++c)
         seed = max(seed, __hip_atomic_load(&part[(r * n_chunks + c) * k_fetch + k_fetch - 1],
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     }
@@ -1119,13 +1120,19 @@ hipError_t launch_score_wide(const rm_index& idx, const void* read_emb, const fl
   uint64_t* part = static_cast<uint64_t*>(ws);
   auto kern = idx.p.precision == RM_FP8_E4M3 ? score_wide_kernel<RM_FP8_E4M3>
                                               : score_wide_kernel<RM_FP16>;
-  const int64_t n_lists = (int64_t)n_reads * p.n_chunks;
-  hipLaunchKernelGGL(clear_wide_kernel, dim3((unsigned)((n_lists + 255) / 256)), dim3(256), 0, st,
-                     part, n_lists, k_fetch);
+  // A block can only start from chunks that others have done: where all blocks
+  // fit on the chip's 256 CUs at once none has, and the entries' launch is saved
+  // (2.5 us of 50).
+  const int n_seeds = (int64_t)p.n_rt * p.n_chunks > 256 ? p.n_chunks : 0;
+  if (n_seeds > 0) {
+    const int64_t n_lists = (int64_t)n_reads * p.n_chunks;
+    hipLaunchKernelGGL(clear_wide_kernel, dim3((unsigned)((n_lists + 255) / 256)), dim3(256), 0,
+                       st, part, n_lists, k_fetch);
+  }
   hipLaunchKernelGGL(kern, dim3((unsigned)p.n_blocks), dim3(kThreads), 0, st,
                      static_cast<const uint8_t*>(read_emb), read_scale, n_reads,
                      static_cast<const uint8_t*>(idx.d_emb), idx.d_scale, idx.n_windows, p.n_rt,
-                     p.n_tiles, p.chunk_tiles, p.n_chunks, k_fetch, part);
+                     p.n_tiles, p.chunk_tiles, p.n_chunks, n_seeds, k_fetch, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(merge_wide_kernel, dim3((unsigned)(((int64_t)n_reads + 3) / 4)), dim3(256), 0,

@@ -928,10 +928,16 @@ __global__ __launch_bounds__(256) void refine_wide_kernel(
     // u = that window's components: P_k = sum over factor k's components of
     // conj(x) u (lane k), S = |u|^2, FP32 sums
     float pr = 0.f, pi = 0.f, sq = 0.f;
+    unsigned long long uR[kWC], uI[kWC];  // loaded before the conversions' branches
 #pragma unroll
     for (int q = 0; q < kWC; ++q) {
-      const float ur = from_fixed(accR[acc_slot(kWC * lane + q)], fits53);
-      const float ui = from_fixed(accI[acc_slot(kWC * lane + q)], fits53);
+      uR[q] = accR[acc_slot(kWC * lane + q)];
+      uI[q] = accI[acc_slot(kWC * lane + q)];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < kWC; ++q) {
+      const float ur = from_fixed(uR[q], fits53), ui = from_fixed(uI[q], fits53);
       pr += __builtin_fmaf(xr[q], ur, xi[q] * ui);
       pi += __builtin_fmaf(xr[q], ui, -(xi[q] * ur));
       sq += __builtin_fmaf(ur, ur, ui * ui);

@@ -104,9 +104,12 @@ __device__ __forceinline__ void sort_and_write(uint64_t key, int lane, int64_t r
 // Three wavefronts per SIMD (the products reuse the table parts' LDS) hide the
 // letters' loads; the fidelities of eight strings are taken together
 // (strings_fidelity).  20,000 reads of 150 letters, 16 candidates: 196 us, 266
-// us with two wavefronts and a wavefront sum per string and term.
+// us with two wavefronts and a wavefront sum per string and term.  24 to 31
+// candidates (RB = 4) have registers for two, where the compiler left to itself
+// takes one: 277 us, 625 us (590 us as before for 16), and 1,000 reads of 6,400
+// letters 622 us, 901 (707).
 template <int RB>
-__global__ __launch_bounds__(256, RB <= 3 ? 3 : 1) void rescore_mfma_kernel(
+__global__ __launch_bounds__(256, RB <= 3 ? 3 : RB == 4 ? 2 : 1) void rescore_mfma_kernel(
     const uint8_t* __restrict__ ref, int64_t W, int N, int stride,
     const float* __restrict__ tab, const uint8_t* __restrict__ seq,
     const int64_t* __restrict__ off, int32_t R, int k_fetch, const int32_t* __restrict__ cand,

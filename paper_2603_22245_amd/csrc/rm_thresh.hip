@@ -96,7 +96,9 @@ __global__ __launch_bounds__(64 * kThrWaves) void window_thresholds_kernel(
     int max_steps, float* __restrict__ thr) {
   __shared__ uint8_t emitted[kThrWaves][64];
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  // uniform, as the draws' products of the window's number are taken to be: on
+  // the VALU they cost 5 % of this kernel
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t j = (int64_t)blockIdx.x * kThrWaves + wave;
   if (j >= W) return;
   const int64_t start = j * stride;

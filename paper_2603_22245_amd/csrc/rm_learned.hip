@@ -33,6 +33,8 @@
 // A step of 1,024 pairs of 150 letters takes 113 us (encoder 32, ranking 6,
 // backward 70, reduction and Adam 5); 706 us with one token at a time on the
 // VALU (189, 84, 416, 13).
+#include <algorithm>
+
 #include "rm_bf16.h"
 #include "rm_internal.h"
 
@@ -308,12 +310,15 @@ __device__ __forceinline__ float fidelity(float4 a, float4 b) {
 }
 
 // Learned encodings c of n_strings strings: out[s][256] (k*4+letter, re/im);
-// for pairs (F not null) also F of strings 2i and 2i + 1.  `per` strings per block.  A string's tokens of
-// one letter fill their own 16-token tiles, so a lane sums its factors over
-// the tiles in registers and the 16 lanes are added once per string and
-// letter.
+// for pairs (F not null) also F of strings 2i and 2i + 1.  A block takes `per`
+// strings at a time.  A string's tokens of one letter fill their own 16-token
+// tiles, so a lane sums its factors over the tiles in registers and the 16 lanes
+// are added once per string and letter.  Where all the strings' tokens of the
+// letter fit one tile they share it, and each string adds the lanes of its own.
 //
-// Bound by VALU issue (the phases and the splits).
+// Bound by VALU issue (the phases and the splits).  100,000 strings of 150
+// letters 1.24 ms (6.9 with a token at a time); of 12 letters, four tokens, 267
+// us (364 with a token at a time, 573 with a tile for each string and letter).
 __global__ __launch_bounds__(64 * kWaves, 2) void learned_encode_kernel(
     const float* __restrict__ params, Strings st, int32_t n_strings, int per, float Nf,
     float inv_n, float turn, float* __restrict__ out, float* __restrict__ F) {
@@ -324,69 +329,90 @@ __global__ __launch_bounds__(64 * kWaves, 2) void learned_encode_kernel(
   __shared__ __align__(16) float c[kStrings][256];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t first = (int64_t)blockIdx.x * per;
-  const int n_own = (int)min<int64_t>(per, n_strings - first);
-  load_net(net, params);
-  if (wave < n_own) {
-    const int n = load_string(letters[wave], st, first + wave, lane);
-    int have[4] = {0, 0, 0, 0};
-    for (int p0 = 0; p0 < n; p0 += 64) {
-      const int mid = p0 + lane < n ? (int)letters[wave][p0 + lane + 4] : 4;
-#pragma unroll
-      for (int L = 0; L < 4; ++L) {
-        const uint64_t m = __ballot(mid == L);
-        if (mid == L)
-          place[L][wave][have[L] + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                       __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] =
-              (uint8_t)(p0 + lane);
-        have[L] += __builtin_popcountll(m);
-      }
-    }
-    if (lane < 4) tokens[lane][wave] = lane == 0 ? have[0] : lane == 1 ? have[1] : lane == 2 ? have[2] : have[3];
-  }
-  __syncthreads();
-
   const int L = wave >> 1, g = lane >> 4;
+  load_net(net, params);
   u32x4 w2[2][2][3];
   load_w2(params, L, lane, w2);
-  for (int s = wave & 1; s < n_own; s += 2) {
-    const int n = tokens[L][s];
-    float re[8], im[8];
+  for (int64_t first = (int64_t)blockIdx.x * per; first < n_strings;
+       first += (int64_t)gridDim.x * per) {
+    const int n_own = (int)min<int64_t>(per, n_strings - first);
+    if (wave < n_own) {
+      const int n = load_string(letters[wave], st, first + wave, lane);
+      int have[4] = {0, 0, 0, 0};
+      for (int p0 = 0; p0 < n; p0 += 64) {
+        const int mid = p0 + lane < n ? (int)letters[wave][p0 + lane + 4] : 4;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) re[i] = im[i] = 0.f;
-    for (int t = 0; t < n; t += 16) {
-      const int i = t + (lane & 15);
-      const bool valid = i < n;
-      const int p = place[L][s][valid ? i : 0];
-      float sn[8], cs[8];
-      const uint8_t* let = &letters[s][p];
-      token_phases(params, net, w2, L, let, flank_fragment(let, g), p, Nf, inv_n, turn, lane, sn, cs);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        re[q] += valid ? cs[q] : 0.f;
-        im[q] += valid ? sn[q] : 0.f;
+        for (int L = 0; L < 4; ++L) {
+          const uint64_t m = __ballot(mid == L);
+          if (mid == L)
+            place[L][wave][have[L] + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0))] =
+                (uint8_t)(p0 + lane);
+          have[L] += __builtin_popcountll(m);
+        }
       }
+      if (lane < 4) tokens[lane][wave] = lane == 0 ? have[0] : lane == 1 ? have[1] : lane == 2 ? have[2] : have[3];
     }
+    __syncthreads();
+
+    int total = 0;
+    for (int s = 0; s < n_own; ++s) total += tokens[L][s];
+    const bool pooled = total <= 16;
+    for (int s = wave & 1; s < n_own; s += 2) {
+      const int n = pooled ? total : tokens[L][s];
+      int from = pooled ? -1 : s;  // the string of the lane's token
+      float re[8], im[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      re[q] = row_sum(re[q]);
-      im[q] = row_sum(im[q]);
-    }
-    if ((lane & 15) == 0) {
+      for (int i = 0; i < 8; ++i) re[i] = im[i] = 0.f;
+      for (int t = 0; t < n; t += 16) {
+        const int i = t + (lane & 15);
+        const bool valid = i < n;
+        int at = valid ? i : 0;
+        if (pooled) {
+          from = 0;
+          while (at >= tokens[L][from]) at -= tokens[L][from++];
+        }
+        const int p = place[L][from][at];
+        float sn[8], cs[8];
+        const uint8_t* let = &letters[from][p];
+        token_phases(params, net, w2, L, let, flank_fragment(let, g), p, Nf, inv_n, turn, lane, sn, cs);
 #pragma unroll
-      for (int q = 0; q < 8; ++q)
-        *reinterpret_cast<float2*>(&c[s][((16 * (q >> 2) + 4 * g + (q & 3)) * 4 + L) * 2]) =
-            make_float2(re[q], im[q]);
+        for (int q = 0; q < 8; ++q) {
+          re[q] += valid ? cs[q] : 0.f;
+          im[q] += valid ? sn[q] : 0.f;
+        }
+      }
+#pragma unroll 1
+      do {  // the string's sums, or those of all this wavefront's strings
+        float sr[8], si[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) sr[q] = si[q] = 0.f;
+        if (tokens[L][s] != 0) {  // uniform
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            sr[q] = row_sum(from == s ? re[q] : 0.f);
+            si[q] = row_sum(from == s ? im[q] : 0.f);
+          }
+        }
+        if ((lane & 15) == 0) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+            *reinterpret_cast<float2*>(&c[s][((16 * (q >> 2) + 4 * g + (q & 3)) * 4 + L) * 2]) =
+                make_float2(sr[q], si[q]);
+        }
+      } while (pooled && (s += 2) < n_own);
     }
-  }
-  __syncthreads();
-  if (wave < n_own)
-    reinterpret_cast<float4*>(out + (first + wave) * 256)[lane] =
-        *reinterpret_cast<const float4*>(&c[wave][4 * lane]);
-  if (F != nullptr && 2 * wave + 1 < n_own) {
-    const float f = fidelity(*reinterpret_cast<const float4*>(&c[2 * wave][4 * lane]),
-                             *reinterpret_cast<const float4*>(&c[2 * wave + 1][4 * lane]));
-    if (lane == 0) F[(first >> 1) + wave] = f;
+    __syncthreads();
+    if (wave < n_own)
+      reinterpret_cast<float4*>(out + (first + wave) * 256)[lane] =
+          *reinterpret_cast<const float4*>(&c[wave][4 * lane]);
+    if (F != nullptr && 2 * wave + 1 < n_own) {
+      const float f = fidelity(*reinterpret_cast<const float4*>(&c[2 * wave][4 * lane]),
+                               *reinterpret_cast<const float4*>(&c[2 * wave + 1][4 * lane]));
+      if (lane == 0) F[(first >> 1) + wave] = f;
+    }
+    // (The next strings' letters and lists were last read before the barrier above,
+    // and their sums are written after the next one.)
   }
 }
 
@@ -827,6 +853,11 @@ __global__ __launch_bounds__(kRedParams * kRedParts) void reduce_adam_kernel(
 static_assert(kRedParams == 64 && RM_LEARNED_MAX_PAIRS <= kRedParams * kRedParts,
               "the loss block's layout");
 
+// Blocks of an encoding, at most: one per CU, which is what their registers allow
+// at a time, so that each splits the weights once (100,000 strings of 12 letters
+// in tiles of their own 482 us, with 4,096 blocks 522).
+constexpr int64_t kEncodeBlocks = 256;
+
 // Strings per block: a block per CU from 1,024 pairs on, two pairs at least.
 int strings_per_block(int64_t n_strings) { return n_strings > 1024 ? kStrings : kStrings / 2; }
 
@@ -860,7 +891,8 @@ hipError_t launch_learned_encode(const float* params, const uint8_t* seq, const 
   }
   const int per = strings_per_block(n_strings);
   const Nominal nom(N);
-  unsigned blocks = (unsigned)(((int64_t)n_strings + per - 1) / per);
+  const int64_t groups = ((int64_t)n_strings + per - 1) / per;
+  const unsigned blocks = (unsigned)std::min<int64_t>(groups, kEncodeBlocks);
   hipLaunchKernelGGL(learned_encode_kernel, dim3(blocks), dim3(64 * kWaves), 0, s, params,
                      Strings{seq, off, nullptr, nullptr}, n_strings, per, nom.n, nom.inv, nom.turn,
                      out, (float*)nullptr);

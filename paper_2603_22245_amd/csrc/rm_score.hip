@@ -5,6 +5,7 @@
 #include "rm_score_kernel.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace rm {
 
@@ -121,11 +122,11 @@ __global__ __launch_bounds__(64 * kMergeWaves) void merge_block_kernel(
 // word names a window, but the bound only uses its F.
 // Without it every chunk of a small launch fills its own lists from nothing
 // (16 to 60 appends and 2 to 4 merges per read and chunk), which took most of
-// the time: 200 reads against 20,000 FP16 windows 465 -> 90 us, 1,000 reads
-// against 100,000 509 -> 230 us, 100 reads against 10^7 2.3 -> 1.1 ms.  Both
+// the time: 200 reads against 20,000 FP16 windows 318 -> 71 us, 1,000 reads
+// against 100,000 339 -> 218 us, 100 reads against 10^7 2.4 -> 1.1 ms.  Both
 // operands come straight from global memory (the block's wavefronts read the
 // same window rows): latency and L1 bound, about a third of the scoring
-// kernel's rate per score, over at most a few percent of its scores.
+// kernel's rate per score; seed_windows weighs that.
 template <int PREC, int KR>
 __global__ __launch_bounds__(512) void seed_kernel(ScoreLaunch L) {
   using RF = RowFmt<PREC, KR>;
@@ -406,6 +407,45 @@ size_t score_workspace_bytes(int precision, int n_groups, const int64_t* W, cons
   return lists + rest;
 }
 
+// Windows that the seed pass samples for a group of `items` work items (0: none).
+//
+// A sample of S windows costs S scores a read, and leaves the lists that start from
+// it about kp W / S keys to take in: the best S grows with the root of kp W.  It is
+// bounded by what many reads pay for it (from 10,000 reads on the best S falls
+// with their number; a 300th of the windows costs 1 % at any), is a power of two
+// (whole rounds of the chip for the pass), and a launch of more than 12 rounds
+// takes none: later rounds start from the earlier ones' slots and the first round's
+// lists cost no more than the sample.  The factors are those of the least time over
+// eight samples of 512 to 65,536 windows and none, 5 to 10 window counts of 1,000
+// to 10^7 by 10 to 14 read counts of 1 to 100,000, in the three precisions and with
+// 8, 16 and 32 keys: in the mean 1.4 % above the best (FP32 0.8 %), 13 % at most
+// (three FP32 launches below 70 us: 20 %).  FP16, 16 keys: without a sample / with
+// this one / with at least 8,192 windows and a 64th of them:
+//   200 reads x 20,000 windows     318     71     84 us
+//   1,000 x 300,000                571    432    431 us
+//   20,000 x 20,000                958    878  1,165 us
+//   100,000 x 5,000              1,726  1,625  2,680 us
+// FP32 scores cost eight times as much against the same lists: 200 x 20,000 288,
+// 149 and 159 us; 20,000 x 5,000 1,238 us without, as here, and 2,311 with 8,192.
+//
+// Groups share the chip's rounds, which leaves more of their lists cold: a 16th of
+// the windows and 8,192 at least (seven groups of 5,000 reads in all, FP8, a
+// reference of 10^7 letters: 11.7 ms without, 7.0 with a single launch's sample,
+// 5.5 with twice that and with the 16th; of 10^6 letters 3.96, 1.33, 1.29 and 1.22).
+static int64_t seed_windows(int precision, int kp, int64_t W, int64_t R, bool grouped,
+                            int64_t items) {
+  if (kp > kScoreSlots || items > 12 * kChipBlocks) return 0;
+  const bool f32 = precision == RM_FP32;
+  const double w = (double)W, r = (double)R;
+  if (grouped && !f32)
+    return (int64_t)std::max(std::min({std::max(w / 16.0, 8192.0), 1e8 / r, 65536.0}), 512.0);
+  const double factor = f32 ? (grouped ? 32.0 : 16.0) : precision == RM_FP16 ? 28.0 : 40.0;
+  double S = std::max(factor * std::sqrt(w * kp / 16.0), f32 ? 0.0 : 1024.0);
+  S = std::min({S, std::max((f32 ? 2.5e6 : 5e7) / r, w / 300.0), 65536.0});
+  if (S < 512.0) return f32 ? 0 : 512;
+  return (int64_t)1 << (int)std::log2(S);
+}
+
 hipError_t launch_score_topk(const rm_index* idx, const ScorePlan& plan,
                              const void* const* read_emb, const float* const* read_scale,
                              const int32_t* R, int k_fetch, int32_t* const* cand_idx,
@@ -433,18 +473,9 @@ hipError_t launch_score_topk(const rm_index* idx, const ScorePlan& plan,
     G.item_begin = item;
     G.thin = gp.thin;
     G.seed_begin = seed_blocks;
-    // Seeding pays while a read's chunks run in few rounds of the chip: with
-    // more than 12 the later rounds start from the earlier ones' slots and the
-    // first round's lists cost less than the sample (20,000 reads against 10^6
-    // windows, 20 rounds: 15.1 ms without, 15.1-15.6 ms with; 5,000 reads, 5
-    // rounds: 4.60 -> 4.30 ms).  A grouped launch, whose groups share the
-    // rounds, takes a larger sample (7 groups of 5,000 reads, FP8: 10.7 ms
-    // without, 7.9 with a 64th, 7.3 with a 32nd).
-    // FP32 scores cost eight times as much against the same lists: two rounds.
-    const int64_t rounds = idx[0].p.precision == RM_FP32 ? 2 : 12;
-    if (plan.kp <= kScoreSlots && (int64_t)gp.read_tiles * gp.chunks <= rounds * kChipBlocks) {
-      const int64_t sample = std::min<int64_t>(
-          std::max<int64_t>(G.W / (plan.n_groups > 1 ? 16 : 64), 8192), 65536);
+    const int64_t sample = seed_windows(idx[0].p.precision, plan.kp, G.W, R[i], plan.n_groups > 1,
+                                        (int64_t)gp.read_tiles * gp.chunks);
+    if (sample > 0) {
       const int64_t n = (std::min(G.W, sample) + kBlkW - 1) / kBlkW, tiles = ((int64_t)R[i] + 127) / 128;
       // 2 to 8 tiles per block, fewer where that fills the chip twice
       G.seed_tiles = (int)std::min<int64_t>(std::max<int64_t>(n * tiles / (2 * kChipBlocks), 2), 8);

@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256, RB <= 3 ? 3 : RB == 4 ? 2 : 1) void rescore_mf
 
   for (int s0 = 0; s0 < S; s0 += SMAX) {
     const int SP = min(SMAX, S - s0);  // strings of this pass
-    uint64_t missing = 0;              // ... that are no string
+    uint64_t present = 0;              // ... that there are
     f32x16 acc[RB][2];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) acc[rb][0] = acc[rb][1] = f32x16{};
@@ -154,24 +154,24 @@ __global__ __launch_bounds__(256, RB <= 3 ? 3 : RB == 4 ? 2 : 1) void rescore_mf
       stage_table_parts(tab, pb, N, tparts, threadIdx.x, 256);
       // this wavefront's strings: the 64 letters at positions pb .. pb+63
       if (active) {
-        // every string's load is issued before the first is used: a string
-        // that is missing reads the reference's first letters instead
+        // every string's load is issued before the first is used; a string that is
+        // missing has none (uniform)
         const int at = min(pb + lane, N - 1);
         uint8_t own[SMAX];
+        present = 0;
 #pragma unroll
         for (int sl = 0; sl < SMAX; ++sl) {
           const int sx = s0 + sl;
           const int32_t j = __builtin_amdgcn_readlane(mycand, max(sx - 1, 0));
-          const bool ok = sl < SP && (sx == 0 ? head_ok : j >= 0 && j < W);
-          const uint8_t* base = !ok ? ref : sx == 0 ? seq + start : ref + (int64_t)j * stride;
-          own[sl] = base[at];
-          if (!ok) missing |= 1ull << sl;
+          own[sl] = 4;
+          if (sl < SP && (sx == 0 ? head_ok : j >= 0 && j < W)) {
+            own[sl] = (sx == 0 ? seq + start : ref + (int64_t)j * stride)[at];
+            present |= 1ull << sl;
+          }
         }
 #pragma unroll
-        for (int sl = 0; sl < SMAX; ++sl) {
-          const bool none = pb + lane >= N || (missing >> sl & 1);
-          letters[sl][lane] = none ? (uint8_t)4 : (uint8_t)min((int)own[sl], 4);
-        }
+        for (int sl = 0; sl < SMAX; ++sl)
+          letters[sl][lane] = pb + lane >= N ? (uint8_t)4 : (uint8_t)min((int)own[sl], 4);
       }
       __syncthreads();
       if (active) {
@@ -203,6 +203,7 @@ __global__ __launch_bounds__(256, RB <= 3 ? 3 : RB == 4 ? 2 : 1) void rescore_mf
     // ---- the fidelities of each row block's strings
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
+      if (s0 + rb > 0 && (present >> (8 * rb) & 0xff) == 0) continue;
       // result block: lane holds column cb*32 + col of rows 8 (v/4) + 4 half + v%4;
       // the indicators were 2, so the sums are halved (exactly)
 #pragma unroll

@@ -31,8 +31,9 @@ constexpr int kMergeKeys = 1024, kMergeKeysWide = 16384;
 // tiles hold 128.
 constexpr int64_t kChipBlocks = 256;
 constexpr int32_t kFewReads = 1024;
-// Reads up to which a launch only streams the index.
-constexpr int32_t kStreamReads = 32;
+// Reads up to which a launch only streams the index; those up to which (a group),
+// or twice which, lists that are not seeded cost little.
+constexpr int32_t kStreamReads = 32, kColdReads = 8;
 
 // Merge the P per-chunk lists of each read into its k_fetch best (keys are
 // unique per read).  One wavefront per read (all its lanes active): each lane
@@ -270,18 +271,31 @@ static void tile_reads(int64_t R, int rt, GroupPlan& gp) {
   }
 }
 
+// Chunks for about 30 items per CU of a 256-CU chip (a short last round), at least
+// 64 tile units each, at most 1024 keys per read for the merge; fewer, longer items
+// leave an uneven last round, more items repeat each read's top-k warm-up in more
+// chunks.
+static int64_t long_chunks(int64_t tiles, int read_tiles, int kp) {
+  const int64_t P = (kChipBlocks * 30 + read_tiles - 1) / read_tiles;
+  return std::max<int64_t>(std::min<int64_t>({P, (tiles + 63) / 64, kMergeKeys / kp}), 1);
+}
+
+// Whether long chunks, `items` of them in a launch and the longest of `longest` tile
+// units, leave CUs idle for more than it costs to fill the lists of shorter ones.
+static bool chip_idle(int precision, int64_t items, int64_t longest, bool only) {
+  if (precision == RM_FP32) return items < 2 * kChipBlocks;
+  return items < kChipBlocks / 2 || (items < kChipBlocks && (only || longest > 256));
+}
+
 // A group's chunks, with chunk_tiles 64-window units per chunk or the default
-// rule (<= 0).  share: the group's part of kChipBlocks by its work.
+// rule (<= 0).  share: the group's part of kChipBlocks by its work; idle: of the
+// launch (chip_idle).
 static void cut_windows(int64_t R, int64_t tiles, int64_t chunk_tiles, int64_t share, bool only,
-                        int kp, GroupPlan& gp) {
+                        bool idle, int precision, int kp, GroupPlan& gp) {
   int64_t ct = chunk_tiles, most = kMergeKeys / kp;
   if (ct <= 0) {
-    // about 30 items per CU of a 256-CU chip (a short last round), at least
-    // 64 tile units each, at most 1024 keys per read for the merge; fewer,
-    // longer items leave an uneven last round, more items repeat each
-    // read's top-k warm-up in more chunks
-    int64_t P = (kChipBlocks * 30 + gp.read_tiles - 1) / gp.read_tiles;
-    P = std::min({P, (tiles + 63) / 64, most});
+    int64_t P = long_chunks(tiles, gp.read_tiles, kp), Q = 0;
+    most = std::max<int64_t>(most, kMergeKeysWide / kp);
     // Few read tiles: that rule gives 64 chunks of 16-key lists at most,
     // and one per 4,096 windows (10 items for 200 FP32 reads against
     // 20,000 windows).  Here a group gets its share of eight items per CU
@@ -292,16 +306,30 @@ static void cut_windows(int64_t R, int64_t tiles, int64_t chunk_tiles, int64_t s
     // Up to 32 reads the launch only streams the index, and shorter
     // chunks cost more than they balance (8 x 10^7: 512 chunks 724 us,
     // 1,024 775 us).
-    most = std::max<int64_t>(most, kMergeKeysWide / kp);
-    int64_t Q = std::min(8 * share / gp.read_tiles, (tiles + 31) / 32);
-    Q = std::max(Q, (share + gp.read_tiles - 1) / gp.read_tiles);
-    if (R <= kStreamReads) Q = std::min<int64_t>(Q, 2 * kChipBlocks);
-    if (only) {
-      const int64_t rounds = (Q * gp.read_tiles + kChipBlocks - 1) / kChipBlocks;
-      Q = std::max(Q, rounds * kChipBlocks / gp.read_tiles);
+    // No seed starts lists of 64 keys (seed_windows): every chunk fills its own
+    // from nothing, so they are only shorter where CUs would be idle, and two
+    // items per CU (FP16 and FP8 groups: one).  FP32 scores cost more against the same
+    // lists; elsewhere few reads of a group take 1,024 windows at least, and
+    // in FP16 a read tile of 17 reads or more 128 chunks at most, unless 256 are one
+    // tile unit each.  With long chunks / eight items per CU / as here: FP16
+    // 3,000 reads x 200,000 windows 2.56 / 3.30 / 2.57 ms, 8,000 x 42,000 1.85 / 2.85 / 1.91,
+    // 60 x 200,000 1.40 / 1.78 / 1.03, 1 x 10^6 1.07 / 0.23 / 0.22; seven groups of 2,950
+    // reads in all, a reference of 226,000 letters, 1.93 / 2.77 / 1.95 (FP32 6.10 /
+    // 5.72 / 4.61), of 300 reads and 400,000 letters 1.36 / 1.35 / 1.16.
+    const bool cold = kp > kScoreSlots, f32 = precision == RM_FP32;
+    if (!cold || idle) {
+      const int64_t own = (share + gp.read_tiles - 1) / gp.read_tiles;
+      Q = std::min((!cold ? 8 : only || f32 ? 2 : 1) * share / gp.read_tiles, (tiles + 31) / 32);
+      Q = std::max(Q, cold && !only && !f32 && R <= kColdReads ? std::min(own, (tiles + 15) / 16) : own);
+      if (R <= kStreamReads) Q = std::min<int64_t>(Q, 2 * kChipBlocks);
+      if (only) {
+        const int64_t rounds = (Q * gp.read_tiles + kChipBlocks - 1) / kChipBlocks;
+        Q = std::max(Q, rounds * kChipBlocks / gp.read_tiles);
+      }
+      if (cold && precision == RM_FP16 && R > 2 * kColdReads && gp.read_tiles == 1 && tiles > most)
+        Q = std::min<int64_t>(Q, kChipBlocks / 2);
     }
     P = std::max(P, std::min({Q, most, tiles}));
-    P = std::max<int64_t>(P, 1);
     ct = (tiles + P - 1) / P;
   }
   if (ct < 1) ct = 1;
@@ -332,10 +360,14 @@ ScorePlan plan_score(int precision, int n_groups, const int64_t* W, const int32_
   p.read_tile = rt;
   p.n_groups = n_groups;
   // work of a group: 64-window units x 128-read halves of its read tiles
-  int64_t work[kMaxGroups], total_work = 0;
+  int64_t work[kMaxGroups], total_work = 0, items1 = 0, longest = 0;
   for (int i = 0; i < n_groups; ++i) {
     GroupPlan& gp = p.g[i];
     tile_reads(R[i], rt, gp);
+    const int64_t tiles = (W[i] + kPlanW - 1) / kPlanW;
+    const int64_t P = long_chunks(tiles, gp.read_tiles, p.kp);
+    items1 += gp.read_tiles * P;
+    longest = std::max(longest, (tiles + P - 1) / P);
     work[i] = (W[i] + kPlanW - 1) / kPlanW * gp.read_tiles * (rt == 256 && !gp.thin ? 2 : 1);
     total_work += work[i];
   }
@@ -344,7 +376,8 @@ ScorePlan plan_score(int precision, int n_groups, const int64_t* W, const int32_
   for (int i = 0; i < n_groups; ++i) {
     GroupPlan& gp = p.g[i];
     cut_windows(R[i], (W[i] + kPlanW - 1) / kPlanW, t.chunk_tiles,
-                (work[i] * kChipBlocks + total_work - 1) / total_work, n_groups == 1, p.kp, gp);
+                (work[i] * kChipBlocks + total_work - 1) / total_work, n_groups == 1,
+                chip_idle(precision, items1, longest, n_groups == 1), precision, p.kp, gp);
     gp.lists_offset = off;
     off += list_bytes((int64_t)R[i] * gp.chunks, p.kp);
     gp.thr_offset = off;
@@ -380,9 +413,13 @@ size_t score_workspace_bytes(int precision, int n_groups, const int64_t* W, cons
     const auto at = [&](int64_t r) {
       GroupPlan g{};
       tile_reads(r, t.read_tile ? t.read_tile : default_read_tile(precision, p.kp, n_groups, r), g);
-      cut_windows(r, tiles, 0, kChipBlocks, n_groups == 1, p.kp, g);
+      const int64_t P = long_chunks(tiles, g.read_tiles, p.kp);
+      const bool idle = n_groups > 1 || chip_idle(precision, g.read_tiles * P, (tiles + P - 1) / P, true);
+      cut_windows(r, tiles, 0, kChipBlocks, n_groups == 1, idle, precision, p.kp, g);
       most = std::max(most, r * g.chunks);
     };
+    at(std::min<int64_t>(R[i], kColdReads));
+    at(std::min<int64_t>(R[i], 2 * kColdReads));
     at(std::min<int64_t>(R[i], kStreamReads));
     for (int64_t r = 128; r < std::min<int64_t>(R[i], kChipBlocks * 30 * 256 + 1); r += 128) at(r);
     at(R[i]);

@@ -452,7 +452,9 @@ size_t score_workspace_bytes(int precision, int n_groups, const int64_t* W, cons
 // with their number; a 300th of the windows costs 1 % at any), is a power of two
 // (whole rounds of the chip for the pass), and a launch of more than 12 rounds
 // takes none: later rounds start from the earlier ones' slots and the first round's
-// lists cost no more than the sample.  The factors are those of the least time over
+// lists cost no more than the sample.  Nor do few windows: with fewer than a list
+// holds a sample bounds nothing (FP16, one window, 200 reads, 16 keys: 41 us without,
+// 50 with it; 100 windows 90 and 60).  The factors are those of the least time over
 // eight samples of 512 to 65,536 windows and none, 5 to 10 window counts of 1,000
 // to 10^7 by 10 to 14 read counts of 1 to 100,000, in the three precisions and with
 // 8, 16 and 32 keys: in the mean 1.4 % above the best (FP32 0.8 %), 13 % at most
@@ -471,7 +473,7 @@ size_t score_workspace_bytes(int precision, int n_groups, const int64_t* W, cons
 // 5.5 with twice that and with the 16th; of 10^6 letters 3.96, 1.33, 1.29 and 1.22).
 static int64_t seed_windows(int precision, int kp, int64_t W, int64_t R, bool grouped,
                             int64_t items) {
-  if (kp > kScoreSlots || items > 12 * kChipBlocks) return 0;
+  if (kp > kScoreSlots || items > 12 * kChipBlocks || W <= 2 * kp) return 0;
   const bool f32 = precision == RM_FP32;
   const double w = (double)W, r = (double)R;
   if (grouped && !f32)

@@ -16,6 +16,8 @@
 // mid + lo) and the indicators are exact in bfloat16, so three bf16 MFMAs with
 // FP32 accumulation reproduce the FP32 direct sums up to the order of FP32
 // additions; each table row is read once per read instead of once per string.
+#include <type_traits>
+
 #include "rm_bf16.h"
 #include "rm_internal.h"
 #include "rm_tokens.h"
@@ -103,11 +105,12 @@ __device__ __forceinline__ void sort_and_write(uint64_t key, int lane, int64_t r
 // [p][col = lane % 32] for the two 32-column blocks of the 64 table reals.
 // Three wavefronts per SIMD (the products reuse the table parts' LDS) hide the
 // letters' loads; the fidelities of eight strings are taken together
-// (strings_fidelity).  20,000 reads of 150 letters, 16 candidates: 196 us, 266
-// us with two wavefronts and a wavefront sum per string and term.  24 to 31
-// candidates (RB = 4) have registers for two, where the compiler left to itself
-// takes one: 277 us, 625 us (590 us as before for 16), and 1,000 reads of 6,400
-// letters 622 us, 901 (707).
+// (strings_fidelity), and which strings a pass holds is one mask, formed once.
+// 20,000 reads of 150 letters, 16 candidates: 174 us, 266 us with two
+// wavefronts, a wavefront sum per string and term and a test per string and
+// chunk.  24 to 31 candidates (RB = 4) have registers for two wavefronts, where the
+// compiler left to itself takes one: 254 us (with tests per chunk 277, and 625 with
+// one wavefront), and 1,000 reads of 6,400 letters 487 us (622 and 901).
 template <int RB>
 __global__ __launch_bounds__(256, RB <= 3 ? 3 : RB == 4 ? 2 : 1) void rescore_mfma_kernel(
     const uint8_t* __restrict__ ref, int64_t W, int N, int stride,
@@ -141,10 +144,17 @@ __global__ __launch_bounds__(256, RB <= 3 ? 3 : RB == 4 ? 2 : 1) void rescore_mf
   float X = 0.f;  // the head's squared norm
   uint64_t mykey = 0;
   const int32_t mycand = active && lane < k_fetch ? cand[r * k_fetch + lane] : -1;
+  const uint64_t windows = __ballot(mycand >= 0 && mycand < W);
+  static_assert(SMAX <= 64, "a pass's strings are a 64-bit mask");
 
   for (int s0 = 0; s0 < S; s0 += SMAX) {
     const int SP = min(SMAX, S - s0);  // strings of this pass
-    uint64_t present = 0;              // ... that there are
+    // ... that there are, bit s - s0
+    const uint64_t present = (s0 == 0 ? windows << 1 | (uint64_t)head_ok : windows >> (s0 - 1)) &
+                             (~0ull >> (64 - SP));
+    int blocks = 0;  // of eight strings that hold one
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) blocks += (present >> (8 * rb) & 0xff) != 0;
     f32x16 acc[RB][2];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) acc[rb][0] = acc[rb][1] = f32x16{};
@@ -154,24 +164,37 @@ __global__ __launch_bounds__(256, RB <= 3 ? 3 : RB == 4 ? 2 : 1) void rescore_mf
       stage_table_parts(tab, pb, N, tparts, threadIdx.x, 256);
       // this wavefront's strings: the 64 letters at positions pb .. pb+63
       if (active) {
-        // every string's load is issued before the first is used; a string that is
-        // missing has none (uniform)
+        // Every string's load is issued before the first is used; a missing one
+        // reads the reference's first letters instead.  With blocks of eight that
+        // hold no string at all, those have no load, and the others' wait for
+        // one another (which costs full lists a quarter of windows of 6,400 letters).
         const int at = min(pb + lane, N - 1);
-        uint8_t own[SMAX];
-        present = 0;
+        auto stage = [&](auto full) {
+          uint32_t own[SMAX];
 #pragma unroll
-        for (int sl = 0; sl < SMAX; ++sl) {
-          const int sx = s0 + sl;
-          const int32_t j = __builtin_amdgcn_readlane(mycand, max(sx - 1, 0));
-          own[sl] = 4;
-          if (sl < SP && (sx == 0 ? head_ok : j >= 0 && j < W)) {
-            own[sl] = (sx == 0 ? seq + start : ref + (int64_t)j * stride)[at];
-            present |= 1ull << sl;
+          for (int rb = 0; rb < RB; ++rb) {
+            if (!decltype(full)::value && (present >> (8 * rb) & 0xff) == 0) {
+#pragma unroll
+              for (int sl = 8 * rb; sl < 8 * rb + 8; ++sl) own[sl] = 4;
+              continue;
+            }
+#pragma unroll
+            for (int sl = 8 * rb; sl < 8 * rb + 8; ++sl) {
+              const int sx = s0 + sl;
+              const int32_t j = __builtin_amdgcn_readlane(mycand, max(sx - 1, 0));
+              const bool ok = present >> sl & 1;
+              const uint8_t* base = !ok ? ref : sx == 0 ? seq + start : ref + (int64_t)j * stride;
+              own[sl] = base[at];
+            }
           }
-        }
 #pragma unroll
-        for (int sl = 0; sl < SMAX; ++sl)
-          letters[sl][lane] = pb + lane >= N ? (uint8_t)4 : (uint8_t)min((int)own[sl], 4);
+          for (int sl = 0; sl < SMAX; ++sl) {
+            const bool none = pb + lane >= N || (present >> sl & 1) == 0;
+            letters[sl][lane] = none ? (uint8_t)4 : (uint8_t)min(own[sl], 4u);
+          }
+        };
+        if (blocks == RB) stage(std::true_type{});
+        else stage(std::false_type{});
       }
       __syncthreads();
       if (active) {

@@ -972,6 +972,9 @@ __global__ __launch_bounds__(256) void refine_wide_kernel(
       // leaving token's, of negated phases, keep the first product's rounding
       // and the entering token's the second's, so the leaving token's lanes take
       // their operands imaginary part first.
+      // A slide may read a sum that another lane changed in the slide before.  The
+      // addresses may alias, so the compiler keeps the loads behind those stores,
+      // and a wavefront's LDS accesses are done in order: no fence between slides.
       const float* x = reinterpret_cast<const float*>(xs);
       unsigned long long *acc0 = enters ? accR : accI, *acc1 = enters ? accI : accR;
       float my_r = 0.f, my_i = 0.f, my_S = 0.f;  // lane i: of start lo + i

@@ -791,9 +791,10 @@ __device__ __forceinline__ void emit_head(float2 a0, float2 a1, float X, int N, 
 // A lane's accumulator holds one read's four letters of one real; the rows
 // are then normalised and stored with one wavefront per read (emit_head).
 //
-// Bound by the FP32 MFMAs (32 cycles per four positions of four reads and 16
-// reals; they hold the VALU, which normalises and stores).  100,000 reads of
-// 150 letters: 125 us, 425 us with one wavefront per read adding its positions
+// Bound by issue: the FP32 MFMAs (32 cycles per four positions of four reads and
+// 16 reals) fill 42 % of the cycles and hold the VALU meanwhile, which forms the
+// one-hot operands, normalises and stores in about as many.  100,000 reads of
+// 150 letters: 120 us, 425 us with one wavefront per read adding its positions
 // one after another; 350 reads of 6,400 letters 110 and 279 us.  RB = 8 reuses
 // each table value for 32 reads; fewer reads take RB = 1, whose longer grid
 // finishes sooner.

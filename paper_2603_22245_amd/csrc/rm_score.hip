@@ -447,8 +447,9 @@ size_t score_workspace_bytes(int precision, int n_groups, const int64_t* W, cons
 // Windows that the seed pass samples for a group of `items` work items (0: none).
 //
 // A sample of S windows costs S scores a read, and leaves the lists that start from
-// it about kp W / S keys to take in: the best S grows with the root of kp W.  It is
-// bounded by what many reads pay for it (from 10,000 reads on the best S falls
+// it about kp W / S keys to take in: the best S grows with the root of W and, since
+// longer lists are also dearer to fill, FP16 and FP8 with kp^(3/4), FP32 with its
+// root.  It is bounded by what many reads pay for it (from 10,000 reads on the best S falls
 // with their number; a 300th of the windows costs 1 % at any), is a power of two
 // (whole rounds of the chip for the pass), and a launch of more than 12 rounds
 // takes none: later rounds start from the earlier ones' slots and the first round's
@@ -457,8 +458,10 @@ size_t score_workspace_bytes(int precision, int n_groups, const int64_t* W, cons
 // 50 with it; 100 windows 90 and 60).  The factors are those of the least time over
 // eight samples of 512 to 65,536 windows and none, 5 to 10 window counts of 1,000
 // to 10^7 by 10 to 14 read counts of 1 to 100,000, in the three precisions and with
-// 8, 16 and 32 keys: in the mean 1.4 % above the best (FP32 0.8 %), 13 % at most
-// (three FP32 launches below 70 us: 20 %).  FP16, 16 keys: without a sample / with
+// 8, 16 and 32 keys: over 957 of these shapes 1.4 % above the best in the mean, 18 %
+// at most in FP16, 30 in FP8 (1,000 reads x 42,000 windows, 32 keys), 28 in FP32 (one
+// read, below 80 us), and at most 12 % above the larger sample below, which is 2.1
+// times the best elsewhere.  FP16, 16 keys: without a sample / with
 // this one / with at least 8,192 windows and a 64th of them:
 //   200 reads x 20,000 windows     318     71     84 us
 //   1,000 x 300,000                571    432    431 us
@@ -479,8 +482,9 @@ static int64_t seed_windows(int precision, int kp, int64_t W, int64_t R, bool gr
   if (grouped && !f32)
     return (int64_t)std::max(std::min({std::max(w / 16.0, 8192.0), 1e8 / r, 65536.0}), 512.0);
   const double factor = f32 ? (grouped ? 32.0 : 16.0) : precision == RM_FP16 ? 28.0 : 40.0;
-  double S = std::max(factor * std::sqrt(w * kp / 16.0), f32 ? 0.0 : 1024.0);
-  S = std::min({S, std::max((f32 ? 2.5e6 : 5e7) / r, w / 300.0), 65536.0});
+  const double lists = kp / 16.0;
+  double S = std::max(factor * std::sqrt(w) * std::pow(lists, f32 ? 0.5 : 0.75), f32 ? 0.0 : 1024.0);
+  S = std::min({S, std::max((f32 ? 2.5e6 : 5e7 * lists) / r, w / 300.0), 65536.0});
   if (S < 512.0) return f32 ? 0 : 512;
   return (int64_t)1 << (int)std::log2(S);
 }

@@ -63,6 +63,7 @@ struct Net {
   u32x4 w1[3][4][64];
   float b1[kHid];
   float b2[kOut];
+  uint32_t odd[5];  // 1 where the wavefront's part of W1, or b1, holds an infinity or no number
 };
 
 __device__ __forceinline__ void load_net(Net& net, const float* __restrict__ p) {
@@ -73,20 +74,34 @@ __device__ __forceinline__ void load_net(Net& net, const float* __restrict__ p) 
     uint32_t part[3][8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) split_bf16x3(src[j], part[0][j], part[1][j], part[2][j]);
+    bool finite = true;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) finite &= fabsf(src[j]) < INFINITY;
+    const uint32_t odd = __ballot(!finite) != 0;
+    if (lane == 0) net.odd[rb] = odd;
 #pragma unroll
     for (int q = 0; q < 3; ++q)
       net.w1[q][rb][lane] =
           u32x4{part[q][0] | part[q][1] << 16, part[q][2] | part[q][3] << 16,
                 part[q][4] | part[q][5] << 16, part[q][6] | part[q][7] << 16};
-  } else if (t < 256 + kHid) {
-    net.b1[t - 256] = p[kB1 + t - 256];
+  } else if (t < 256 + kHid) {  // the fifth wavefront
+    const float b = p[kB1 + t - 256];
+    net.b1[t - 256] = b;
+    const uint32_t odd = __ballot(!(fabsf(b) < INFINITY)) != 0;
+    if (t == 256) net.odd[4] = odd;
   } else if (t < 256 + kHid + kOut) {
     net.b2[t - 256 - kHid] = p[kB2 + t - 256 - kHid];
   }
 }
 
-// max(x, 0) as one integer maximum (a positive NaN stays; fmaxf would take two
-// instructions to quiet it).
+// Whether W1 or b1 holds an infinity or no number; uniform, after the barrier.
+__device__ __forceinline__ bool odd_net(const Net& net) {
+  return __builtin_amdgcn_readfirstlane(net.odd[0] | net.odd[1] | net.odd[2] | net.odd[3] |
+                                        net.odd[4]) != 0;
+}
+
+// max(x, 0) as one integer maximum (a positive NaN would stay, but settle leaves
+// none; fmaxf would take two instructions to quiet it).
 __device__ __forceinline__ float relu(float x) {
   return __uint_as_float((uint32_t)max(__float_as_int(x), 0));
 }
@@ -156,22 +171,25 @@ __device__ __forceinline__ u32x4 flank_fragment(const uint8_t* let, int g) {
 // A pre-activation this close to zero (a few dozen ulps of the summands) is
 // summed again in FP32 in the order of the flanks, so that its sign -- whether
 // the unit is on and passes gradients -- does not depend on how the matrix
-// cores add.  About one tile in 400 has one.
+// cores add.  About one tile in 400 has one.  With a weight that is infinite or no
+// number all are: a product with a one-hot zero would spread it over every token,
+// and a sum of the chosen weights leaves it to those that choose it, where a unit
+// that is no number is off.
 constexpr float kNearZero = 1.0f / 1048576.0f;
 
 // Settles a lane's 16 pre-activations h[i / 4][i % 4]: unit(i) is the hidden unit
 // and letters(i) the 9-mer of entry i.  One at a time, so that the rare path
 // needs few registers.
 template <typename Unit, typename Letters>
-__device__ __forceinline__ void settle(const float* __restrict__ p, f32x4 (&h)[4], Unit unit,
-                                       Letters letters) {
-  float least = 1.f;
+__device__ __forceinline__ void settle(const float* __restrict__ p, bool every, f32x4 (&h)[4],
+                                       Unit unit, Letters letters) {
+  float least = every ? 0.f : 1.f;
 #pragma unroll
   for (int i = 0; i < 16; ++i) least = fminf(least, fabsf(h[i >> 2][i & 3]));
   if (!__ballot(least < kNearZero)) return;
   uint32_t todo = 0;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) todo |= (uint32_t)(fabsf(h[i >> 2][i & 3]) < kNearZero) << i;
+  for (int i = 0; i < 16; ++i) todo |= (uint32_t)(every || fabsf(h[i >> 2][i & 3]) < kNearZero) << i;
 #pragma unroll 1
   while (todo) {
     const int at = __builtin_ctz(todo);
@@ -184,6 +202,7 @@ __device__ __forceinline__ void settle(const float* __restrict__ p, f32x4 (&h)[4
       const int f = let[i + (i > 3)];
       if (f < 4) pre += p[kW1 + u * kIn + 4 * i + f];
     }
+    pre = isnan(pre) ? 0.f : pre;
 #pragma unroll
     for (int i = 0; i < 16; ++i) h[i >> 2][i & 3] = at == i ? pre : h[i >> 2][i & 3];
   }
@@ -213,7 +232,7 @@ __device__ __forceinline__ void load_w2(const float* __restrict__ p, int L, int 
 // values: the phase is off by at most 5e-7 (1e-7 root mean square) for offsets
 // up to 10^5 rad.  Scaled at once the offset alone would cost 4.4e-7 at 8 rad
 // and 1.0e-6 at 20, and the FP32 sum of both angles 2.8e-7 and 5.4e-7.
-__device__ __forceinline__ void token_phases(const float* __restrict__ params, const Net& net,
+__device__ __forceinline__ void token_phases(const float* __restrict__ params, const Net& net, bool every,
                                              const u32x4 (&w2)[2][2][3], int L, const uint8_t* let,
                                              const u32x4& x, int p, float Nf, float inv_n,
                                              float turn, int lane, float (&sn)[8], float (&cs)[8]) {
@@ -225,7 +244,7 @@ __device__ __forceinline__ void token_phases(const float* __restrict__ params, c
 #pragma unroll
     for (int q = 2; q >= 0; --q) h[rb] = mfma32(net.w1[q][rb][lane], x, h[rb]);  // small parts first
   }
-  settle(params, h, [&](int i) { return 16 * (i >> 2) + 4 * g + (i & 3); },
+  settle(params, every, h, [&](int i) { return 16 * (i >> 2) + 4 * g + (i & 3); },
          [&](int) { return let; });
   u32x4 hp[2][3];
 #pragma unroll
@@ -355,6 +374,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void learned_encode_kernel(
     }
     __syncthreads();
 
+    const bool every = odd_net(net);
     int total = 0;
     for (int s = 0; s < n_own; ++s) total += tokens[L][s];
     const bool pooled = total <= 16;
@@ -375,7 +395,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void learned_encode_kernel(
         const int p = place[L][from][at];
         float sn[8], cs[8];
         const uint8_t* let = &letters[from][p];
-        token_phases(params, net, w2, L, let, flank_fragment(let, g), p, Nf, inv_n, turn, lane, sn, cs);
+        token_phases(params, net, every, w2, L, let, flank_fragment(let, g), p, Nf, inv_n, turn, lane, sn, cs);
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
           re[q] += valid ? cs[q] : 0.f;
@@ -626,6 +646,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void learned_backward_kernel(
   __syncthreads();
 
   const int L = wave >> 1, g = lane >> 4, col = lane & 15;
+  const bool every = odd_net(net);
   int n_tok = 0;
   for (int s = 0; s < n_own; ++s) n_tok += tokens[L][s];
   u32x4 w2[2][2][3];
@@ -649,7 +670,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void learned_backward_kernel(
     float dd[8];
     {
       float sn[8], cs[8];
-      token_phases(params, net, w2, L, &letters[s][p], x, p, Nf, inv_n, turn, lane, sn, cs);
+      token_phases(params, net, every, w2, L, &letters[s][p], x, p, Nf, inv_n, turn, lane, sn, cs);
 #pragma unroll
       for (int ob = 0; ob < 2; ++ob)
 #pragma unroll
@@ -694,7 +715,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void learned_backward_kernel(
 #pragma unroll
       for (int q = 2; q >= 0; --q) hid[cb] = mfma32(x, net.w1[q][cb][lane], hid[cb]);
     }
-    settle(params, hid, [&](int i) { return 16 * (i >> 2) + col; },
+    settle(params, every, hid, [&](int i) { return 16 * (i >> 2) + col; },
            [&](int i) {
              const int ei = list[L][min(t + 4 * g + (i & 3), n_tok - 1)];
              return &letters[ei >> 8][ei & 255];
